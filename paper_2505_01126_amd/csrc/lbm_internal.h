@@ -87,10 +87,11 @@ hipError_t launch_init(const Params &p, int storage, void *fout, void *phi_out, 
 // tile: workgroup tile width in x, 64 (64 x 4 sites) or 32 (32 x 8)
 // fix: phi held as int32 fixed point (two-phase only)
 // phys: buoyancy / phase-dependent relaxation time compiled in (two-phase only)
-int batch_grid(int storage, bool tp, bool frc, bool ml, bool fix, bool phys, int tile);
+// nt: non-temporal stores of the outputs (tile 64 only)
+int batch_grid(int storage, bool tp, bool frc, bool ml, bool fix, bool phys, int tile, bool nt);
 hipError_t launch_step_batch(const Params *tab, const Buffers *buf, const uint32_t *first, int nbox,
                              uint32_t *counter, int parity, int storage, bool tp, bool frc, bool ml, bool fix,
-                             bool phys, int tile, int grid, hipStream_t s);
+                             bool phys, int tile, bool nt, int grid, hipStream_t s);
 // the learned-curvature pass ahead of the step (fix: fixed-point phi)
 int mlp_pass_grid(bool fix, int tile);
 hipError_t launch_mlp_pass_batch(const Params *tab, const Buffers *buf, const uint32_t *first, int nbox,

@@ -6,15 +6,15 @@
 
 namespace lbm {
 
-extern template int step_grid<0>(bool, bool, bool, bool, bool, int);
-extern template int step_grid<1>(bool, bool, bool, bool, bool, int);
-extern template int step_grid<2>(bool, bool, bool, bool, bool, int);
+extern template int step_grid<0>(bool, bool, bool, bool, bool, int, bool);
+extern template int step_grid<1>(bool, bool, bool, bool, bool, int, bool);
+extern template int step_grid<2>(bool, bool, bool, bool, bool, int, bool);
 extern template hipError_t step_launch<0>(const Params *, const Buffers *, const uint32_t *, int, uint32_t *, int, bool,
-                                          bool, bool, bool, bool, int, int, hipStream_t);
+                                          bool, bool, bool, bool, int, bool, int, hipStream_t);
 extern template hipError_t step_launch<1>(const Params *, const Buffers *, const uint32_t *, int, uint32_t *, int, bool,
-                                          bool, bool, bool, bool, int, int, hipStream_t);
+                                          bool, bool, bool, bool, int, bool, int, hipStream_t);
 extern template hipError_t step_launch<2>(const Params *, const Buffers *, const uint32_t *, int, uint32_t *, int, bool,
-                                          bool, bool, bool, bool, int, int, hipStream_t);
+                                          bool, bool, bool, bool, int, bool, int, hipStream_t);
 
 // ----------------------------------------------------------- initial state
 // f^0 = f^eq(p*0, u0) + w H : A0 / (2 c_s^4), A0 = -c_s^2 tau (grad u0 + grad u0^T),
@@ -105,6 +105,7 @@ __device__ __forceinline__ void site_state(const Params &P, const void *fin_, co
     auto site_at = [&](int dx, int dy, int dz) { return zk[1 + dz] * plane + yk[1 + dy] + xk[1 + dx]; };
     M10 M;
     PhiGrad G;
+    float cs = 0.f;
     float ph[27];
     float kfd = 0.f, gn = 0.f;
     bool sel = false;
@@ -116,20 +117,25 @@ __device__ __forceinline__ void site_state(const Params &P, const void *fin_, co
         if constexpr (TP) {
 #pragma unroll
             for (int i = 0; i < 27; i++) ph[i] = (float)phi_load(phi, site_at(CX(i), CY(i), CZ(i)), P.phi_fix);
-            phi_stencil(ph, G);
+            M10 Mp;
+            phi_stencil(ph, Mp, G);
+            cs = surface_coef<ML>(Mp, G, P);
             if constexpr (ML) sel = mlp_select(G, P, kfd, gn);
         }
     }
     float fs[3] = {0.f, 0.f, 0.f};
+    float yv[4] = {0.f, 0.f, 0.f, 0.f};
     if constexpr (ML) {
-        float yv[4] = {0.f, 0.f, 0.f, 0.f};
         mlp_wave(W, wv, sel, ph, yv, lane);
+    }
+    if constexpr (TP) {
         if (valid) {
-            if (sel) surface_blend(G, P, kfd, gn, yv, fs);
-            else surface_fd(G, P, fs);
+#pragma unroll
+            for (int a = 0; a < 3; a++) fs[a] = cs * G.g[a];
+            if constexpr (ML) {
+                if (sel) surface_blend(G, cs, P, kfd, gn, yv, fs);
+            }
         }
-    } else if constexpr (TP) {
-        if (valid) surface_fd(G, P, fs);
     }
     if (valid) {
         float aext[3] = {0.f, 0.f, 0.f};
@@ -300,22 +306,22 @@ __global__ void __launch_bounds__(NTHREADS) k_reduce_final(const double *partial
 }
 
 // --------------------------------------------------------------- launchers
-int batch_grid(int storage, bool tp, bool frc, bool ml, bool fix, bool phys, int tile)
+int batch_grid(int storage, bool tp, bool frc, bool ml, bool fix, bool phys, int tile, bool nt)
 {
-    if (storage == 0) return step_grid<0>(tp, frc, ml, fix, phys, tile);
-    if (storage == 1) return step_grid<1>(tp, frc, ml, fix, phys, tile);
-    return step_grid<2>(tp, frc, ml, fix, phys, tile);
+    if (storage == 0) return step_grid<0>(tp, frc, ml, fix, phys, tile, nt);
+    if (storage == 1) return step_grid<1>(tp, frc, ml, fix, phys, tile, nt);
+    return step_grid<2>(tp, frc, ml, fix, phys, tile, nt);
 }
 
 hipError_t launch_step_batch(const Params *tab, const Buffers *buf, const uint32_t *first, int nbox,
                              uint32_t *counter, int parity, int storage, bool tp, bool frc, bool ml, bool fix,
-                             bool phys, int tile, int grid, hipStream_t s)
+                             bool phys, int tile, bool nt, int grid, hipStream_t s)
 {
     if (storage == 0)
-        return step_launch<0>(tab, buf, first, nbox, counter, parity, tp, frc, ml, fix, phys, tile, grid, s);
+        return step_launch<0>(tab, buf, first, nbox, counter, parity, tp, frc, ml, fix, phys, tile, nt, grid, s);
     if (storage == 1)
-        return step_launch<1>(tab, buf, first, nbox, counter, parity, tp, frc, ml, fix, phys, tile, grid, s);
-    return step_launch<2>(tab, buf, first, nbox, counter, parity, tp, frc, ml, fix, phys, tile, grid, s);
+        return step_launch<1>(tab, buf, first, nbox, counter, parity, tp, frc, ml, fix, phys, tile, nt, grid, s);
+    return step_launch<2>(tab, buf, first, nbox, counter, parity, tp, frc, ml, fix, phys, tile, nt, grid, s);
 }
 
 int mlp_pass_grid(bool fix, int tile)

@@ -151,16 +151,21 @@ template <> struct PhiStore<true> {
     __device__ static T add(T q, Acc d) { return (int32_t)((uint32_t)q + d); }
 };
 
-// Raw buffer access to one z plane of populations (27 rows of nx * ny): the
-// row offset i * plane goes in the scalar offset, the in-plane offset in the
-// vector offset, so no per-row vector address arithmetic is needed.
+// Raw buffer access to one z plane of a field (of populations: 27 rows of
+// nx * ny): row offsets go in the scalar offset, the offset in the row in the
+// vector offset, so no vector address arithmetic is needed.  (Global loads with
+// the same scalar base took a 64-bit vector addition and two registers per
+// address: the compiler extends the offsets to 64 bits outside the loop.)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *base, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
 }
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <class T> __device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    if constexpr (sizeof(T) == 4)
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+    else if constexpr (sizeof(T) == 4)
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
     else
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0));
@@ -177,24 +182,13 @@ constexpr int STORE_NT = 2;
 template <class T, int AUX = 0>
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, T v)
 {
-    if constexpr (sizeof(T) == 4)
+    if constexpr (sizeof(T) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, AUX);
+    else if constexpr (sizeof(T) == 4)
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, AUX);
     else
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, voff, soff, AUX);
 }
-template <class T> __device__ __forceinline__ void gstore(LBM_GLOBAL T *p, T v, bool nt)
-{
-    if (nt)
-        __builtin_nontemporal_store(v, p);
-    else
-        *p = v;
-}
-// gstore at a 32-bit byte offset from a wave-uniform base (see ldg)
-template <class T> __device__ __forceinline__ void gstb(LBM_GLOBAL T *base, uint32_t byte_off, T v, bool nt)
-{
-    gstore((LBM_GLOBAL T *)((LBM_GLOBAL char *)base + byte_off), v, nt);
-}
-
 // ------------------------------------------------------ separable moments
 // Ten sums M_abc = 216 sum_c w(c) v(c) cx^a cy^b cz^c (a + b + c <= 2) of 27
 // lattice-ordered values, taken axis by axis (x, then y, then z); along each
@@ -203,42 +197,48 @@ struct M10 {
     float m000, m100, m010, m001, m200, m020, m002, m110, m101, m011;
 };
 
-__device__ __forceinline__ void moments10(const float (&v)[27], M10 &M)
+// The sums over one z plane of the 3 x 3 x 3 stencil (rows of cy = -1, 0, 1):
+// p_ab = sum over the plane with weights cx^a cy^b.
+struct P6 {
+    float p00, p01, p02, p10, p11, p20;
+};
+__device__ __forceinline__ void plane6(const float *v, P6 &p)
 {
-    float r0[9], r1[9], r2[9];
+    float r0[3], r1[3], r2[3];
 #pragma unroll
-    for (int row = 0; row < 9; row++) {
+    for (int row = 0; row < 3; row++) {
         const float vm = v[3 * row], v0 = v[3 * row + 1], vp = v[3 * row + 2];
         r2[row] = vp + vm;
         r1[row] = vp - vm;
         r0[row] = fmaf(4.0f, v0, r2[row]);
     }
-    float p00[3], p01[3], p02[3], p10[3], p11[3], p20[3];
+    p.p02 = r0[2] + r0[0];
+    p.p00 = fmaf(4.0f, r0[1], p.p02);
+    p.p01 = r0[2] - r0[0];
+    p.p10 = fmaf(4.0f, r1[1], r1[2] + r1[0]);
+    p.p11 = r1[2] - r1[0];
+    p.p20 = fmaf(4.0f, r2[1], r2[2] + r2[0]);
+}
+// the ten sums from the plane sums below (a), at (b) and above (c)
+__device__ __forceinline__ void planes10(const P6 &a, const P6 &b, const P6 &c, M10 &M)
+{
+    M.m002 = c.p00 + a.p00;
+    M.m000 = fmaf(4.0f, b.p00, M.m002);
+    M.m001 = c.p00 - a.p00;
+    M.m010 = fmaf(4.0f, b.p01, c.p01 + a.p01);
+    M.m011 = c.p01 - a.p01;
+    M.m020 = fmaf(4.0f, b.p02, c.p02 + a.p02);
+    M.m100 = fmaf(4.0f, b.p10, c.p10 + a.p10);
+    M.m101 = c.p10 - a.p10;
+    M.m110 = fmaf(4.0f, b.p11, c.p11 + a.p11);
+    M.m200 = fmaf(4.0f, b.p20, c.p20 + a.p20);
+}
+__device__ __forceinline__ void moments10(const float (&v)[27], M10 &M)
+{
+    P6 p[3];
 #pragma unroll
-    for (int z = 0; z < 3; z++) {
-        const int a = 3 * z, b = 3 * z + 1, c = 3 * z + 2;
-        float s = r0[c] + r0[a];
-        p00[z] = fmaf(4.0f, r0[b], s);
-        p01[z] = r0[c] - r0[a];
-        p02[z] = s;
-        s = r1[c] + r1[a];
-        p10[z] = fmaf(4.0f, r1[b], s);
-        p11[z] = r1[c] - r1[a];
-        p20[z] = fmaf(4.0f, r2[b], r2[c] + r2[a]);
-    }
-    float s = p00[2] + p00[0];
-    M.m000 = fmaf(4.0f, p00[1], s);
-    M.m001 = p00[2] - p00[0];
-    M.m002 = s;
-    s = p01[2] + p01[0];
-    M.m010 = fmaf(4.0f, p01[1], s);
-    M.m011 = p01[2] - p01[0];
-    M.m020 = fmaf(4.0f, p02[1], p02[2] + p02[0]);
-    s = p10[2] + p10[0];
-    M.m100 = fmaf(4.0f, p10[1], s);
-    M.m101 = p10[2] - p10[0];
-    M.m110 = fmaf(4.0f, p11[1], p11[2] + p11[0]);
-    M.m200 = fmaf(4.0f, p20[1], p20[2] + p20[0]);
+    for (int z = 0; z < 3; z++) plane6(v + 9 * z, p[z]);
+    planes10(p[0], p[1], p[2], M);
 }
 
 // ------------------------------------------------------- per-site physics
@@ -257,46 +257,61 @@ struct PhiGrad {
     float phi, g[3], H[6];
 };
 
-__device__ __forceinline__ void phi_stencil(const float (&ph)[27], PhiGrad &G)
+__device__ __forceinline__ void phi_grad(const M10 &M, float phi, PhiGrad &G)
 {
-    M10 M;
-    moments10(ph, M);
-    const float k1 = 1.0f / 72.0f, k2 = 1.0f / 24.0f, t = M.m000 * (1.0f / 3.0f);
-    G.phi = ph[13];
+#pragma clang fp contract(off)
+    const float k1 = 1.0f / 72.0f, k2 = 1.0f / 24.0f, third = -1.0f / 3.0f;
+    G.phi = phi;
     G.g[0] = M.m100 * k1;
     G.g[1] = M.m010 * k1;
     G.g[2] = M.m001 * k1;
-    G.H[0] = (M.m200 - t) * k2;
-    G.H[1] = (M.m020 - t) * k2;
-    G.H[2] = (M.m002 - t) * k2;
+    G.H[0] = fmaf(third, M.m000, M.m200) * k2;
+    G.H[1] = fmaf(third, M.m000, M.m020) * k2;
+    G.H[2] = fmaf(third, M.m000, M.m002) * k2;
     G.H[3] = M.m110 * k2;
     G.H[4] = M.m101 * k2;
     G.H[5] = M.m011 * k2;
+}
+__device__ __forceinline__ void phi_stencil(const float (&ph)[27], M10 &M, PhiGrad &G)
+{
+    moments10(ph, M);
+    phi_grad(M, ph[13], G);
 }
 
 // Surface-tension force with the finite-difference curvature (Sec. 2.3 CSF
 // form): F^s = -(3 delta/2) sigma K |g| g, with K |g| = tr H - g.H.g / |g|^2
 // (K = div n, n = g/|g| toward phi = 1); zero where |g| <= 1e-12.
-__device__ __forceinline__ void surface_fd(const PhiGrad &G, const Params &P, float (&fs)[3])
+// surface_coef gives the factor of g.
+// The roundings are written out (contraction-free), so that every kernel forms
+// the same bits; with the learned curvature (ML) |g|^2 and tr H are those of
+// its criterion.
+template <bool ML> __device__ __forceinline__ float surface_coef(const M10 &M, const PhiGrad &G, const Params &P)
 {
+#pragma clang fp contract(off)
     const float *g = G.g, *H = G.H;
-    const float g2 = g[0] * g[0] + g[1] * g[1] + g[2] * g[2];
+    const float k2 = 1.0f / 24.0f, third = -1.0f / 3.0f;
+    const float g2 = ML ? g[0] * g[0] + g[1] * g[1] + g[2] * g[2] : fmaf(g[2], g[2], fmaf(g[0], g[0], g[1] * g[1]));
     float cs = 0.f;
     if (g2 > 1e-24f) {
-        const float trH = H[0] + H[1] + H[2];
-        const float gHg = g[0] * (H[0] * g[0] + H[3] * g[1] + H[4] * g[2]) +
-                          g[1] * (H[3] * g[0] + H[1] * g[1] + H[5] * g[2]) +
-                          g[2] * (H[4] * g[0] + H[5] * g[1] + H[2] * g[2]);
-        cs = -P.fs_coef * (trH - gHg * __builtin_amdgcn_rcpf(g2));
+        const float trH = ML ? (H[0] + H[1]) + H[2]
+                             : fmaf(k2, fmaf(third, M.m000, M.m002), fmaf(k2, fmaf(third, M.m000, M.m200), H[1]));
+        const float hx = fmaf(H[4], g[2], fmaf(H[3], g[1], H[0] * g[0]));
+        const float hy = fmaf(H[5], g[2], fmaf(H[3], g[0], H[1] * g[1]));
+        const float hz = fmaf(H[2], g[2], fmaf(H[4], g[0], H[5] * g[1]));
+        const float gHg = fmaf(g[2], hz, fmaf(g[0], hx, g[1] * hy));
+        cs = -P.fs_coef * fmaf(-__builtin_amdgcn_rcpf(g2), gHg, trH);
     }
-#pragma unroll
-    for (int a = 0; a < 3; a++) fs[a] = cs * g[a];
+    return cs;
 }
-
 // Learned curvature: K_FD and |g| at the site, and whether the network is
 // consulted (interface cell 0.02 < phi < 0.98 with |K_FD| > k_lo).
 // (The learned-curvature helpers are contraction-free, so that every inlined
 // copy -- single-box and batch kernels -- rounds identically.)
+__device__ __forceinline__ float grad_norm(const PhiGrad &G)
+{
+#pragma clang fp contract(off)
+    return sqrtf(G.g[0] * G.g[0] + G.g[1] * G.g[1] + G.g[2] * G.g[2]);
+}
 __device__ __forceinline__ bool mlp_select(const PhiGrad &G, const Params &P, float &kfd, float &gn)
 {
 #pragma clang fp contract(off)
@@ -317,15 +332,16 @@ __device__ __forceinline__ bool mlp_select(const PhiGrad &G, const Params &P, fl
 // Blend of the network output y = (K, n) with the finite-difference K and n:
 // s = smoothstep((|K_FD| - k_lo) / (k_hi - k_lo)), K = s K_net + (1 - s) K_FD,
 // n_s = normalise(s n_net/|n_net| + (1 - s) g/|g|), F^s = -(3 delta/2) sigma K |g|^2 n_s;
-// the finite-difference force is kept when the output is non-finite or
-// |n_net| is outside [0.5, 1.5].
-__device__ __forceinline__ void surface_blend(const PhiGrad &G, const Params &P, float kfd, float gn,
+// the finite-difference force (cs_fd g) is kept when the output is non-finite
+// or |n_net| is outside [0.5, 1.5].
+__device__ __forceinline__ void surface_blend(const PhiGrad &G, float cs_fd, const Params &P, float kfd, float gn,
                                               const float (&y)[4], float (&fs)[3])
 {
 #pragma clang fp contract(off)
     const float nn = sqrtf(y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
     if (!(isfinite(y[0]) && isfinite(nn) && nn >= 0.5f && nn <= 1.5f)) {
-        surface_fd(G, P, fs);
+#pragma unroll
+        for (int a = 0; a < 3; a++) fs[a] = cs_fd * G.g[a];
         return;
     }
     const float t = fminf((fabsf(kfd) - P.k_lo) / (P.k_hi - P.k_lo), 1.0f);
@@ -504,12 +520,12 @@ __device__ __forceinline__ float face_flux(float v0, float v1, float v2, float v
 // w_I [6 D (phi_a - phi_b) + 3 kappa (Q_a + Q_b) . c_I]; the projection on c_I
 // takes the nonzero components in x, y, z order.
 template <int I>
-__device__ __forceinline__ float link_flux(float pa, float pb, const float4 &qa, const float4 &qb, float d6w,
+__device__ __forceinline__ float link_flux(float pa, float pb, const float (&qa)[3], const float (&qb)[3], float d6w,
                                            float k3w)
 {
 #pragma clang fp contract(off)
     constexpr int cx = CX(I), cy = CY(I), cz = CZ(I);
-    const float tx = qa.x + qb.x, ty = qa.y + qb.y, tz = qa.z + qb.z;
+    const float tx = qa[0] + qb[0], ty = qa[1] + qb[1], tz = qa[2] + qb[2];
     float s;
     if constexpr (cx != 0) {
         s = cx > 0 ? tx : -tx;
@@ -524,36 +540,37 @@ __device__ __forceinline__ float link_flux(float pa, float pb, const float4 &qa,
     return fmaf(k3w, s, d6w * (pa - pb));
 }
 
-// Q = phi (1 - phi) n, n = g / |g| (zero where |g| <= 1e-12), g from the
-// separable first moments (g = M1 / 72; n needs only M1).  Neighbouring
+// Q = phi (1 - phi) n, n = g / |g| (zero where |g| <= 1e-12), from the first
+// moments M1 of the phi stencil (g = M1 / 72; n needs only M1).  Neighbouring
 // workgroups, and the prologue and body of one workgroup, evaluate Q at the
 // same point from different inlined copies: contraction-free, so every copy
 // rounds identically.
-__device__ __forceinline__ void q_of(const float (&v)[27], float (&q)[3])
+__device__ __forceinline__ void q_of(float Mx, float My, float Mz, float phi, float (&q)[3])
 {
 #pragma clang fp contract(off)
-    float d[9], m[9];
-#pragma unroll
-    for (int row = 0; row < 9; row++) {
-        d[row] = v[3 * row + 2] - v[3 * row];
-        m[row] = fmaf(4.0f, v[3 * row + 1], v[3 * row + 2] + v[3 * row]);
-    }
-    float dx[3], ey[3], sy[3];
-#pragma unroll
-    for (int z = 0; z < 3; z++) {
-        dx[z] = fmaf(4.0f, d[3 * z + 1], d[3 * z + 2] + d[3 * z]);
-        ey[z] = m[3 * z + 2] - m[3 * z];
-        sy[z] = fmaf(4.0f, m[3 * z + 1], m[3 * z + 2] + m[3 * z]);
-    }
-    const float Mx = fmaf(4.0f, dx[1], dx[2] + dx[0]);
-    const float My = fmaf(4.0f, ey[1], ey[2] + ey[0]);
-    const float Mz = sy[2] - sy[0];
     const float m2 = fmaf(Mx, Mx, fmaf(My, My, Mz * Mz));
-    const float c = v[13] * (1.0f - v[13]);
+    const float c = phi * (1.0f - phi);
     const float s = m2 > 5.184e-21f ? c * __frsqrt_rn(m2) : 0.0f;  // |g| > 1e-12 <=> |M1| > 7.2e-11
     q[0] = s * Mx;
     q[1] = s * My;
     q[2] = s * Mz;
+}
+// plane sums for the first moments alone
+struct P3 {
+    float p00, p01, p10;
+};
+__device__ __forceinline__ void plane3(const float *v, P3 &p)
+{
+    float r0[3], r1[3];
+#pragma unroll
+    for (int row = 0; row < 3; row++) {
+        const float vm = v[3 * row], v0 = v[3 * row + 1], vp = v[3 * row + 2];
+        r1[row] = vp - vm;
+        r0[row] = fmaf(4.0f, v0, vp + vm);
+    }
+    p.p00 = fmaf(4.0f, r0[1], r0[2] + r0[0]);
+    p.p01 = r0[2] - r0[0];
+    p.p10 = fmaf(4.0f, r1[1], r1[2] + r1[0]);
 }
 
 // ----------------------------------------------------------------- forcing
@@ -597,11 +614,13 @@ template <int TW> struct Tile {
     static constexpr int PX = X + 2 * HX, PY = Y + 2 * HY;
     static constexpr int PLANE = PX * PY;         // phi values per staged plane
     static constexpr int QX = X + 2, QY = Y + 2;  // Q tile (halo 1)
-    static constexpr int QPLANE = QX * QY;
     static constexpr int LOADS = (PLANE + NTHREADS - 1) / NTHREADS;
-    static constexpr int QPTS = (QPLANE + NTHREADS - 1) / NTHREADS;
-    static constexpr int NXF = Y * (X + 1);       // x faces of a plane tile (left of each site + 1)
-    static constexpr int NYF = (Y + 1) * X;       // y faces
+    static constexpr int QHALO = QX * QY - NTHREADS;  // points of the Q tile's halo ring
+    // Q, x faces and y faces are held with the row stride of the phi tile, so
+    // that one LDS address per thread (its phi tile index) serves all of them:
+    // rows HY-1 .. of the tile for Q, rows HY .. for the faces
+    static constexpr int Q0 = (HY - 1) * PX, QN = QY * PX;
+    static constexpr int F0 = HY * PX, NXF = Y * PX, NYF = (Y + 1) * PX;
 };
 
 __device__ __forceinline__ int ring(int z) { return (z + 4 * NRING) % NRING; }
@@ -616,9 +635,25 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
+// No instruction moves across: the scheduler otherwise starts the LDS reads of
+// many links and faces at once, for which the step has no registers, and a
+// spilled register read back waits for every load in flight before it.
+__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+
 // Software pipeline over the z planes of a chunk: while plane z is processed,
 // the phi plane z+4, the face velocities of plane z+1, the 27 populations of
 // plane z+1 and the site's own phi and u_z ahead are already being fetched.
+//
+// What bounds it: with 16-bit populations the vector instructions (937 per site
+// and plane, issued 88 % of the time with three waves per SIMD), with FP32 ones
+// the memory traffic.  Hence: the phi stencil is summed plane by plane, each
+// plane once for the Q, the gradient and the Hessian of the three planes it
+// enters (summed anew for each, they were 110 instructions more); every address
+// is a scalar base plus one of three 32-bit columns; and the wait counts are
+// exact, so that neither the stores of a plane nor the loads of the next are
+// waited for before they are needed.  512^3 bubbly HIT, per step: FP16 5.0 ->
+// 4.6 ms; 256^3 single phase FP16 0.575 -> 0.47 ms; Runge-Kutta stage at 256^3
+// 0.385 -> 0.35 ms; FP32 at 512^3 6.9 ms as before.
 // One work item: the xy tile and z chunk with linear index L (x tile fastest,
 // then y tile, then z chunk) of one box.  Every thread of the workgroup calls
 // it; it leaves no LDS state that the next call relies on.
@@ -626,8 +661,8 @@ __device__ __forceinline__ void lds_barrier()
 // ACO (Allen-Cahn only): one Runge-Kutta stage of the phase field and nothing
 // else: phi_out = rk_a phi^n + rk_b (phi_in + L(phi_in)) with phi_in staged in
 // the LDS ring (B.phin), phi^n read at the site (B.phin0), FP64 phi.
-template <int S, bool TP, bool FRC, bool ML, int TW = TX, bool LATE_PF = (S == 0), bool FX = false,
-          bool ACO = false, bool PH = false>
+template <int S, bool TP, bool FRC, bool ML, int TW = TX, bool NT = false, bool FX = false, bool ACO = false,
+          bool PH = false>
 __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, const uint32_t L, double rk_a = 0.0,
                                           double rk_b = 1.0)
 {
@@ -645,15 +680,8 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
     using PT = typename PS::T;
     using AT = typename PS::Acc;
     using TL = Tile<TW>;
-    constexpr int TXW = TL::X, TYW = TL::Y, PX = TL::PX, PLANE = TL::PLANE, QX = TL::QX, QPLANE = TL::QPLANE,
-                  LOADS = TL::LOADS, QPTS = TL::QPTS, NXF = TL::NXF, NYF = TL::NYF;
-    // Where the next plane's populations are fetched: 16-bit values pack two
-    // to a register, so FP16/BF16 fetch right after the moments (longest
-    // prefetch distance) and still fit three waves per SIMD; FP32 fetches after
-    // the phase-field work, the shorter live range that fits three waves.  The
-    // batch kernel, which holds a few more registers for its work queue, fetches
-    // late in every storage mode (a spilled prefetch register would stall).
-    constexpr bool kLatePrefetch = TP && LATE_PF;
+    constexpr int TXW = TL::X, TYW = TL::Y, PX = TL::PX, PLANE = TL::PLANE, QX = TL::QX, LOADS = TL::LOADS,
+                  QHALO = TL::QHALO, Q0 = TL::Q0, F0 = TL::F0;
     constexpr uint32_t ES = sizeof(T);
     const int nx = P.nx, ny = P.ny, nz = P.nz;
     const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
@@ -669,31 +697,48 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
     // unconditional, so the compiler counts the loads in flight exactly instead
     // of draining all of them (stores included) before the next plane.
     const int xg = (x0 + tx) % nx, yg = (y0 + ty) % ny;
-    // every tile row of populations, u and phi fills whole 128-byte lines
-    const bool nt_rows = (TW * ES) % 128 == 0 && nx % 64 == 0;
     const T *__restrict__ fin = (const T *)B.fin;
     T *__restrict__ fout = (T *)B.fout;
-    const LBM_GLOBAL float *__restrict__ ux_in = gconst(B.uin);
-    const LBM_GLOBAL float *__restrict__ uy_in = ux_in + N;
-    const LBM_GLOBAL float *__restrict__ uz_in = ux_in + 2 * (size_t)N;
-    const LBM_GLOBAL PT *__restrict__ phin = gconst((const PT *)B.phin);
-    LBM_GLOBAL PT *__restrict__ phout = gmut((PT *)B.phout);
-    LBM_GLOBAL float *__restrict__ uout = gmut(B.uout);
+    const float *__restrict__ uin = B.uin;  // component a at a * N
+    const PT *__restrict__ phin = (const PT *)B.phin;
 
-    // with one x-row per wave the row is wave-uniform (scalar forcing loads)
-    const int yw = TW == 64 ? __builtin_amdgcn_readfirstlane(yg) : yg;
-    uint32_t src_xy[9];
+    // The periodic neighbours' columns xs and rows ys (k = 1 + offset).  With
+    // one x-row per wave (TW = 64) the row is wave-uniform: it goes into the
+    // scalar part of every address, and the vector part is one of three
+    // columns.  Two rows per wave (TW = 32) take the row in the vector part.
+    constexpr bool ROW = TW == 64;
+    const int yw = ROW ? __builtin_amdgcn_readfirstlane(yg) : yg;
+    uint32_t xs[3], ys[3];
 #pragma unroll
-    for (int dy = -1; dy <= 1; dy++)
-#pragma unroll
-        for (int dx = -1; dx <= 1; dx++)
-            src_xy[(dy + 1) * 3 + dx + 1] = (uint32_t)wrapi(yg - dy, ny) * nx + (uint32_t)wrapi(xg - dx, nx);
-    const uint32_t own_xy = (uint32_t)yg * nx + xg;
+    for (int k = 0; k < 3; k++) {
+        xs[k] = (uint32_t)wrapi(xg + k - 1, nx);
+        ys[k] = (uint32_t)wrapi(yw + k - 1, ny) * (uint32_t)nx;
+    }
+    auto srow = [&](int k) { return ROW ? ys[k] : 0u; };                            // scalar part
+    auto vcol = [&](int ky, int kx) { return ROW ? xs[kx] : ys[ky] + xs[kx]; };  // vector part
+    const uint32_t own_v = vcol(1, 1);
+    auto zp = [&](int z) { return (uint32_t)z * plane; };  // first site of plane z (below 2^30)
+    // buffer over plane z of a field of one value per site
+    auto field = [&](auto *base, int z) { return plane_rsrc(base + zp(z), plane * (uint32_t)sizeof(*base)); };
+    // element of a field at plane z, row ky and column kx of the neighbourhood
+    auto at = [&](auto *base, int z, int ky, int kx) {
+        using E = std::remove_cv_t<std::remove_reference_t<decltype(*base)>>;
+        return bload<E>(field(base, z), vcol(ky, kx) * (uint32_t)sizeof(E), srow(ky) * (uint32_t)sizeof(E));
+    };
+    auto put = [&](auto *base, int z, auto v) {  // own site
+        bstore<decltype(v), NT ? STORE_NT : 0>(field(base, z), own_v * (uint32_t)sizeof(v),
+                                               srow(1) * (uint32_t)sizeof(v), v);
+    };
 
+    // The x twiddles of the body force: in LDS with the phase field (read once
+    // per plane there; four registers less to carry through it), in registers
+    // without
+    __shared__ float4 sex[FRC && TP ? TXW : 1];
     float4 ex = {0.f, 0.f, 0.f, 0.f};
     if constexpr (FRC) {
         const LBM_GLOBAL float *fx = gconst((const float *)P.fx) + 4 * xg;
         ex = make_float4(fx[0], fx[1], fx[2], fx[3]);
+        if (TP && ty == 0) sex[tx] = ex;
     }
     const uint32_t yrow = (uint32_t)yw;
 
@@ -706,164 +751,241 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
     // prefetch synchronous
     using HT = std::conditional_t<sizeof(T) == 2, uint32_t, T>;
     HT hv[27];
-    const size_t pstride = (size_t)27 * plane;  // elements per z plane of populations
     const uint32_t pbytes = 27u * plane * ES;   // bytes per z plane of populations
+    // steps of the row offset from one population to the next: the next x, and
+    // from the last x of row y + 1, y, y - 1 to the first of the row after it
+    const uint32_t pstep = plane * ES, rstep01 = pstep + (srow(1) - srow(2)) * ES,
+                   rstep10 = pstep + (srow(0) - srow(1)) * ES, rstep12 = pstep + (srow(2) - srow(0)) * ES;
     auto fetch_pops = [&](int z) {
-        const __amdgpu_buffer_rsrc_t zsrc[3] = {plane_rsrc(fin + (size_t)wrapi(z + 1, nz) * pstride, pbytes),
-                                                plane_rsrc(fin + (size_t)z * pstride, pbytes),
-                                                plane_rsrc(fin + (size_t)wrapi(z - 1, nz) * pstride, pbytes)};
-        // running row offset, kept opaque so that the 27 offsets are not all
-        // precomputed into scalar registers
-        uint32_t soff = 0;
+        const __amdgpu_buffer_rsrc_t zsrc[3] = {plane_rsrc(fin + (size_t)zp(wrapi(z + 1, nz)) * 27, pbytes),
+                                                plane_rsrc(fin + (size_t)zp(z) * 27, pbytes),
+                                                plane_rsrc(fin + (size_t)zp(wrapi(z - 1, nz)) * 27, pbytes)};
+        // running offset of the population's row, kept opaque so that the 27
+        // offsets are not all precomputed into scalar registers
+        uint32_t soff = srow(2) * ES;
 #pragma unroll
         for (int i = 0; i < 27; i++) {
+            const uint32_t v = vcol(1 - CY(i), 1 - CX(i)) * ES;
             if constexpr (std::is_same_v<HT, T>)
-                hv[i] = bload<T>(zsrc[CZ(i) + 1], src_xy[(CY(i) + 1) * 3 + CX(i) + 1] * ES, soff);
+                hv[i] = bload<T>(zsrc[CZ(i) + 1], v, soff);
             else
-                hv[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(zsrc[CZ(i) + 1],
-                                                                       src_xy[(CY(i) + 1) * 3 + CX(i) + 1] * ES, soff, 0);
-            soff += plane * ES;
+                hv[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(zsrc[CZ(i) + 1], v, soff, 0);
+            soff += CX(i) < 1 ? pstep : (CY(i) < 0 ? rstep01 : (CY(i) < 1 ? rstep10 : rstep12));
             asm volatile("" : "+s"(soff));
         }
     };
 
-    // LDS: phi ring (FP32), Q planes z-1..z+1, x/y face fluxes of plane z, and
-    // the global xy offset of every position of the phi tile
+    // LDS: phi ring (FP32), Q of planes z-1..z+1, x/y advective face fluxes of plane z
     __shared__ float sphi[TP ? NRING : 1][TP ? PLANE : 1];
-    constexpr bool AC = TP;  // the Allen-Cahn update runs here
-    __shared__ float4 sq[AC ? 3 : 1][AC ? QPLANE : 1];  // Q (x, y, z, unused) per point
-    __shared__ float sjx[AC ? NXF : 1];
-    __shared__ float sjy[AC ? NYF : 1];
-    __shared__ uint32_t sxy[TP ? PLANE : 1];
+    constexpr int QN = TP ? TL::QN : 1;
+    __shared__ float sq[TP ? 3 : 1][3][QN];
+    __shared__ float sjx[TP ? TL::NXF : 1];
+    __shared__ float sjy[TP ? TL::NYF : 1];
+    // plane sums of the halo points: each point's three sums of the last two
+    // planes and the next, read and written by its own thread only (kept in
+    // registers they made the step spill)
+    __shared__ float sh[TP ? 3 : 1][3][TP ? QHALO : 1];
     const int lc = (ty + HY) * PX + (tx + HX);  // own phi tile index
-    const int qc = (ty + 1) * QX + (tx + 1);    // own Q tile index
-    int q_lds[QPTS];
     PT phn[LOADS];          // prefetched phi plane
+    uint32_t p_off[LOADS];  // byte offsets of its points in a plane
+    // Q is evaluated at the own site by every thread and at the halo ring of
+    // the tile by the waves after the first; the first wave has the y faces
+    // above the top row instead, so that no SIMD of the CU (wave i of a
+    // workgroup runs on SIMD i) has both.
+    static_assert(QHALO <= NTHREADS - 64, "one halo point per thread");
+    const int hp = tid - 64;
+    const bool halo = TP && hp >= 0 && hp < QHALO;
+    int h_lc = lc;
+    if (halo) {
+        const int k = hp - 2 * QX;
+        const int qy = hp < QX ? 0 : (hp < 2 * QX ? TYW + 1 : 1 + (k >> 1));
+        const int qx = hp < QX ? hp : (hp < 2 * QX ? hp - QX : (k & 1) * (QX - 1));
+        h_lc = (qy + HY - 1) * PX + (qx + HX - 1);
+    }
     // The x and y faces of a plane tile are evaluated in three rounds, each
     // wave taking one direction in each: (A) the x face left of every site,
     // (B) the y face below every site, (C) the y faces above the top row
     // (threads 0 .. TXW-1, the first wave) and the x faces right of the last
-    // column (threads 64 .. 64+TYW-1, the second wave).  c_lc: the phi tile
+    // column (the first threads of the last wave).  c_lc: the phi tile
     // index of the left (lower) cell of a round-C face.
-    const bool c_top = tid < TXW, c_right = tid >= 64 && tid < 64 + TYW;
-    const int c_lc = c_top ? (TYW - 1 + HY) * PX + tid + HX : (tid - 64 + HY) * PX + (TXW - 1 + HX);
+    constexpr int RIGHT0 = NTHREADS - 64;
+    const bool c_top = tid < TXW, c_right = tid >= RIGHT0 && tid < RIGHT0 + TYW;
+    const int c_lc = c_top ? (TYW - 1 + HY) * PX + tid + HX : (tid - RIGHT0 + HY) * PX + (TXW - 1 + HX);
     float fa_l, fa_r, fb_l, fb_r, fc_l = 0.f, fc_r = 0.f;  // prefetched face velocities
+    // the round-C face's velocities in plane 0 (per-lane pointers: the two kinds
+    // of face read different components)
+    const LBM_GLOBAL float *c_l = nullptr, *c_r = nullptr;
     float jz_left = 0.f, uz_c = 0.f, uz_n = 0.f;
     PT po = 0;              // prefetched own phi
+    // carried from plane to plane: the phi stencil's plane sums of the two
+    // planes below the next one (own site), so that every plane is summed once
+    // for the Q, the gradient and the Hessian of three planes
+    P6 pa, pb;
+    // the phi gradient and curvature (its coefficient in the force; with the
+    // learned curvature K_FD) of the current and the next plane, read and
+    // written by its own thread only (in registers they made the step spill)
+    __shared__ float4 sg[LBM && TP ? 2 : 1][LBM && TP ? NTHREADS : 1];
+    float cs = 0.f, csn = 0.f;        // learned curvature: the coefficient ...
+    bool sel = false, seln = false;   // ... and whether the network is consulted
 
-    auto fetch_plane = [&](int z) {
-        const LBM_GLOBAL PT *src = phin + (size_t)modi(z, nz) * plane;
-#pragma unroll
-        for (int k = 0; k < LOADS; k++) {
-            const int e = tid + k * NTHREADS;
-            if (e < PLANE) phn[k] = src[sxy[e]];
-        }
+    // in-plane offset of position e of the phi tile
+    auto tile_xy = [&](int e) {
+        const int ly = e / PX, lx = e - ly * PX;
+        return (uint32_t)modi(y0 + ly - HY, ny) * nx + (uint32_t)modi(x0 + lx - HX, nx);
     };
-    auto store_plane = [&](int z) {
+    auto fetch_plane = [&](PT(&r)[LOADS], int z) {
+        const __amdgpu_buffer_rsrc_t src = field(phin, wrapi(z, nz));
+#pragma unroll
+        for (int k = 0; k < LOADS; k++) r[k] = bload<PT>(src, p_off[k], 0);
+    };
+    auto store_plane = [&](const PT(&r)[LOADS], int z) {
         float *dst = sphi[ring(z)];
 #pragma unroll
         for (int k = 0; k < LOADS; k++) {
             const int e = tid + k * NTHREADS;
-            if (e < PLANE) dst[e] = PS::f32(phn[k]);
+            if (e < PLANE) dst[e] = PS::f32(r[k]);
         }
     };
-    // (64-bit per-lane addresses: the scalar-base form of ldg made these loads
-    // cost the FP32 step 0.8 %)
     auto fetch_face_u = [&](int z) {
-        const uint32_t zo = (uint32_t)z * plane;
-        fa_l = ux_in[zo + src_xy[5]];
-        fa_r = ux_in[zo + own_xy];
-        fb_l = uy_in[zo + src_xy[7]];
-        fb_r = uy_in[zo + own_xy];
-        if (c_top) {
-            fc_l = uy_in[zo + sxy[c_lc]];
-            fc_r = uy_in[zo + sxy[c_lc + PX]];
-        } else if (c_right) {
-            fc_l = ux_in[zo + sxy[c_lc]];
-            fc_r = ux_in[zo + sxy[c_lc + 1]];
+        const __amdgpu_buffer_rsrc_t ux = field(uin, z), uy = field(uin + N, z);
+        fa_l = bload<float>(ux, vcol(1, 0) * 4u, srow(1) * 4u);
+        fa_r = bload<float>(ux, own_v * 4u, srow(1) * 4u);
+        fb_l = bload<float>(uy, vcol(0, 1) * 4u, srow(0) * 4u);
+        fb_r = bload<float>(uy, own_v * 4u, srow(1) * 4u);
+        if (c_top || c_right) {
+            fc_l = c_l[zp(z)];
+            fc_r = c_r[zp(z)];
         }
     };
+    auto load9 = [&](const float *p, float (&v)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; i++) v[i] = p[(i / 3 - 1) * PX + i % 3 - 1];
+    };
+    auto put3 = [&](int z, const P3 &n) {
+        auto &h = sh[(z + 3) % 3];
+        h[0][hp] = n.p00;
+        h[1][hp] = n.p01;
+        h[2][hp] = n.p10;
+    };
+    // q of plane z (phi planes z-1 .. z+1: the carried sums and the newest
+    // plane) and, from the same moments, the own site's phi gradient and Hessian
     auto compute_q = [&](int z) {
-        const float *p0 = sphi[ring(z - 1)];
-        const float *p1 = sphi[ring(z)];
-        const float *p2 = sphi[ring(z + 1)];
-        const int slot = (z + 3) % 3;
+        const float *pc = sphi[ring(z)], *pn = sphi[ring(z + 1)];
+        float(*q)[QN] = sq[(z + 3) % 3];
+        float v[9], qv[3];
+        {
+            P6 n;
+            M10 M;
+            load9(pn + lc, v);
+            plane6(v, n);
+            planes10(pa, pb, n, M);
+            pa = pb;
+            pb = n;
+            const float c = pc[lc];
+            q_of(M.m100, M.m010, M.m001, c, qv);
 #pragma unroll
-        for (int k = 0; k < QPTS; k++) {
-            const int p = tid + k * NTHREADS;
-            if (p < QPLANE) {
-                const int c = q_lds[k];
-                float st[27];
-#pragma unroll
-                for (int i = 0; i < 27; i++) {
-                    const float *pl = CZ(i) < 0 ? p0 : (CZ(i) > 0 ? p2 : p1);
-                    st[i] = pl[c + CY(i) * PX + CX(i)];
+            for (int a = 0; a < 3; a++) q[a][lc - Q0] = qv[a];
+            if constexpr (LBM) {
+                PhiGrad G;
+                phi_grad(M, c, G);
+                csn = surface_coef<ML>(M, G, P);
+                float w = csn;
+                if constexpr (ML) {
+                    float gn;
+                    seln = mlp_select(G, P, w, gn);
                 }
-                float q[3];
-                q_of(st, q);
-                sq[slot][p] = make_float4(q[0], q[1], q[2], 0.0f);
+                sg[z & 1][tid] = make_float4(G.g[0], G.g[1], G.g[2], w);
             }
+        }
+        if (halo) {
+            P3 n;
+            load9(pn + h_lc, v);
+            plane3(v, n);
+            const auto &a3 = sh[(z + 2) % 3], &b3 = sh[(z + 3) % 3];
+            q_of(fmaf(4.0f, b3[2][hp], n.p10 + a3[2][hp]), fmaf(4.0f, b3[1][hp], n.p01 + a3[1][hp]),
+                 n.p00 - a3[0][hp], pc[h_lc], qv);
+            put3(z + 1, n);
+#pragma unroll
+            for (int a = 0; a < 3; a++) q[a][h_lc - Q0] = qv[a];
         }
     };
     // advective x and y fluxes of plane z through the faces of the tile, each
-    // face once: x face f of row r lies between tile columns f-1 and f
-    // (f = 0..TXW), y face r of column x between tile rows r-1 and r (r = 0..TYW)
+    // face once, held at the tile index of the cell right of (above) it
     auto compute_faces = [&](int z) {
         const float *pl = sphi[ring(z)];
         {
             const float *p = pl + lc - 3;  // cells x-3 .. x+2 of the row
-            sjx[ty * (TXW + 1) + tx] = face_flux(p[0], p[1], p[2], p[3], p[4], p[5], fa_l, fa_r);
+            sjx[lc - F0] = face_flux(p[0], p[1], p[2], p[3], p[4], p[5], fa_l, fa_r);
         }
+        sched_fence();
         {
             const float *p = pl + lc - 3 * PX;  // cells y-3 .. y+2 of the column
-            sjy[ty * TXW + tx] = face_flux(p[0], p[PX], p[2 * PX], p[3 * PX], p[4 * PX], p[5 * PX], fb_l, fb_r);
+            sjy[lc - F0] = face_flux(p[0], p[PX], p[2 * PX], p[3 * PX], p[4 * PX], p[5 * PX], fb_l, fb_r);
         }
         if (c_top) {
             const float *p = pl + c_lc - 2 * PX;
-            sjy[TYW * TXW + tid] = face_flux(p[0], p[PX], p[2 * PX], p[3 * PX], p[4 * PX], p[5 * PX], fc_l, fc_r);
+            sjy[c_lc + PX - F0] = face_flux(p[0], p[PX], p[2 * PX], p[3 * PX], p[4 * PX], p[5 * PX], fc_l, fc_r);
         } else if (c_right) {
             const float *p = pl + c_lc - 2;
-            sjx[(tid - 64) * (TXW + 1) + TXW] = face_flux(p[0], p[1], p[2], p[3], p[4], p[5], fc_l, fc_r);
+            sjx[c_lc + 1 - F0] = face_flux(p[0], p[1], p[2], p[3], p[4], p[5], fc_l, fc_r);
         }
     };
-
-
+    if (LBM && !TP) fetch_pops(z0);
     if constexpr (TP) {
 #pragma unroll
         for (int k = 0; k < LOADS; k++) {
             const int e = tid + k * NTHREADS;
-            const int ly = e / PX, lx = e - ly * PX;
-            if (e < PLANE) sxy[e] = (uint32_t)modi(y0 + ly - HY, ny) * nx + (uint32_t)modi(x0 + lx - HX, nx);
+            p_off[k] = tile_xy(e < PLANE ? e : PLANE - 1) * (uint32_t)sizeof(PT);  // spare lanes re-read the last
         }
+        const LBM_GLOBAL float *uc = gconst(uin) + (c_top ? (size_t)N : 0);
+        c_l = uc + tile_xy(c_lc);
+        c_r = uc + tile_xy(c_top ? c_lc + PX : c_lc + 1);
+        {
+            // the six planes below the loop's first one, all in flight at once
+            PT r[6][LOADS];
 #pragma unroll
-        for (int k = 0; k < QPTS; k++) {
-            const int p = tid + k * NTHREADS;
-            const int qy = p / QX, qx = p - qy * QX;
-            q_lds[k] = (qy + 2) * PX + (qx + 2);  // phi tile centre of Q point (qx, qy)
+            for (int j = 0; j < 6; j++) fetch_plane(r[j], z0 - 3 + j);
+            fetch_plane(phn, z0 + 3);
+            fetch_face_u(z0);
+#pragma unroll
+            for (int j = 0; j < 6; j++) store_plane(r[j], z0 - 3 + j);
         }
-        for (int z = z0 - 3; z <= z0 + 2; z++) {
-            fetch_plane(z);
-            store_plane(z);
-        }
-        fetch_plane(z0 + 3);
+        if (LBM) fetch_pops(z0);
         lds_barrier();
         {
-            fetch_face_u(z0);
+            float v[9];
+            load9(sphi[ring(z0 - 2)] + lc, v);
+            plane6(v, pa);
+            load9(sphi[ring(z0 - 1)] + lc, v);
+            plane6(v, pb);
+            if (halo)
+                for (int z = z0 - 2; z < z0; z++) {
+                    P3 n;
+                    load9(sphi[ring(z)] + h_lc, v);
+                    plane3(v, n);
+                    put3(z, n);
+                }
             compute_q(z0 - 1);
             compute_q(z0);
+            cs = csn;
+            sel = seln;
             // z face below the first plane: cells z0-3 .. z0+2, velocities at z0-1, z0
-            const float um = uz_in[(uint32_t)modi(z0 - 1, nz) * plane + own_xy];
-            uz_c = uz_in[(uint32_t)z0 * plane + own_xy];
-            uz_n = ldg(uz_in + (size_t)wrapi(z0 + 1, nz) * plane, own_xy * 4u);
-            po = phin[(size_t)z0 * plane + own_xy];
-            float v[6];
+            const float um = at(uin + 2 * (size_t)N, wrapi(z0 - 1, nz), 1, 1);
+            uz_c = at(uin + 2 * (size_t)N, z0, 1, 1);
+            uz_n = at(uin + 2 * (size_t)N, wrapi(z0 + 1, nz), 1, 1);
+            po = at(phin, z0, 1, 1);
+            float c[6];
 #pragma unroll
-            for (int k = 0; k < 6; k++) v[k] = sphi[ring(z0 - 3 + k)][lc];
-            jz_left = face_flux(v[0], v[1], v[2], v[3], v[4], v[5], um, uz_c);
+            for (int k = 0; k < 6; k++) c[k] = sphi[ring(z0 - 3 + k)][lc];
+            jz_left = face_flux(c[0], c[1], c[2], c[3], c[4], c[5], um, uz_c);
         }
     }
-    if (LBM) fetch_pops(z0);
-
+    // Every load of the prologue is complete when the loop begins.  The compiler
+    // counts the operations issued since a load on the way into the loop and
+    // around it and waits for the smaller number; on the way in no stores
+    // follow the population loads, so without this wait every plane of the
+    // loop waited for the stores of the plane before.
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), expcnt / lgkmcnt untouched
     for (int z = z0; z < zend; z++) {
         const bool more = z + 1 < zend;
         // The prefetches for the next plane run in the last plane of the chunk
@@ -873,20 +995,17 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
         // populations and the other prefetched values on both sides of the branch.
         const int zn = more ? z + 1 : z;
         if constexpr (TP) {
-            store_plane(z + 3);
-            fetch_plane(zn + 3);
+            store_plane(phn, z + 3);
+            fetch_plane(phn, zn + 3);
             lds_barrier();
             compute_q(z + 1);
+            sched_fence();
             compute_faces(z);
+            sched_fence();
             fetch_face_u(zn);
             lds_barrier();
         }
-        const uint32_t own = (uint32_t)z * plane + own_xy;
         M10 M;
-        PhiGrad G;
-        float ph[27];
-        float kfd = 0.f, gn = 0.f;
-        bool sel = false;
         float aext[3] = {0.f, 0.f, 0.f};
         float y[4] = {0.f, 0.f, 0.f, 0.f};  // learned curvature: network output at a selected cell
         {
@@ -899,14 +1018,13 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
                 }
                 moments10(hf, M);
             }
-            if (LBM && !kLatePrefetch) fetch_pops(zn);
-
+            if (LBM && !TP) fetch_pops(zn);
             if constexpr (TP) {
                 // Allen-Cahn: phi^{n+1} = phi^n - sum (outgoing - incoming) face and link fluxes
                 // four independent partial sums keep the dependent add chains short
                 AT acc[4];
-                acc[0] = PS::flux(sjx[ty * (TXW + 1) + tx]) - PS::flux(sjx[ty * (TXW + 1) + tx + 1]);
-                acc[0] += PS::flux(sjy[ty * TXW + tx]) - PS::flux(sjy[(ty + 1) * TXW + tx]);
+                acc[0] = PS::flux(sjx[lc - F0]) - PS::flux(sjx[lc - F0 + 1]);
+                acc[0] += PS::flux(sjy[lc - F0]) - PS::flux(sjy[lc - F0 + PX]);
                 {
                     float v[6];
 #pragma unroll
@@ -915,48 +1033,48 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
                     acc[1] = PS::flux(jz_left) - PS::flux(jr);
                     jz_left = jr;
                     uz_c = uz_n;
-                    uz_n = ldg(uz_in + (size_t)wrapi(zn + 1, nz) * plane, own_xy * 4u);
+                    uz_n = at(uin + 2 * (size_t)N, wrapi(zn + 1, nz), 1, 1);
                 }
+                sched_fence();
                 {
-                    // phase-field stencil of this site (LDS)
-                    const float *pm = sphi[ring(z - 1)];
-                    const float *pc = sphi[ring(z)];
-                    const float *pp = sphi[ring(z + 1)];
+                    const float *pm = sphi[ring(z - 1)] + lc, *pc = sphi[ring(z)] + lc, *pp = sphi[ring(z + 1)] + lc;
+                    auto q_at = [&](int k, int off, float(&q)[3]) {
 #pragma unroll
-                    for (int i = 0; i < 27; i++) {
-                        const float *pl = CZ(i) < 0 ? pm : (CZ(i) > 0 ? pp : pc);
-                        ph[i] = pl[lc + CY(i) * PX + CX(i)];
-                    }
-                    if constexpr (!ACO) phi_stencil(ph, G);
-                    if constexpr (ML) sel = mlp_select(G, P, kfd, gn);
-                    const float4 *q0 = sq[(z - 1 + 3) % 3];
-                    const float4 *q1 = sq[(z + 3) % 3];
-                    const float4 *q2 = sq[(z + 1 + 3) % 3];
-                    const float4 qo = q1[qc];
+                        for (int a = 0; a < 3; a++) q[a] = sq[(z + k + 3) % 3][a][lc - Q0 + off];
+                    };
+                    float qo[3];
+                    q_at(0, 0, qo);
+                    const float p0 = pc[0];
                     const float d6w[4] = {0.f, P.d6 * WT(14), P.d6 * WT(15), P.d6 * WT(26)};
                     const float k3w[4] = {0.f, P.k3 * WT(14), P.k3 * WT(15), P.k3 * WT(26)};
                     // links 14 and 15 open the partial sums 2 and 3
 #define LB_LINK(I)                                                                                    \
     {                                                                                                 \
-        const float4 qn = (CZ(I) > 0 ? q2 : q1)[qc + CY(I) * QX + CX(I)];                             \
-        const float4 qs = (CZ(I) > 0 ? q0 : q1)[qc - CY(I) * QX - CX(I)];                             \
-        const float fo = link_flux<I>(ph[13], ph[I], qo, qn, d6w[C2(I)], k3w[C2(I)]);                 \
-        const float fi = link_flux<I>(ph[26 - I], ph[13], qs, qo, d6w[C2(I)], k3w[C2(I)]);            \
+        constexpr int off = CY(I) * PX + CX(I), up = CZ(I) > 0;                                       \
+        float qn[3], qs[3];                                                                           \
+        q_at(up, off, qn);                                                                            \
+        q_at(-up, -off, qs);                                                                          \
+        const float fo = link_flux<I>(p0, (up ? pp : pc)[off], qo, qn, d6w[C2(I)], k3w[C2(I)]);       \
+        const float fi = link_flux<I>((up ? pm : pc)[-off], p0, qs, qo, d6w[C2(I)], k3w[C2(I)]);      \
         const AT d = PS::flux(fi) - PS::flux(fo);                                                     \
         if constexpr (I == 14 || I == 15) acc[I & 3] = d;                                             \
         else acc[I & 3] += d;                                                                         \
     }
-                    LB_LINK(14) LB_LINK(15) LB_LINK(16) LB_LINK(17) LB_LINK(18) LB_LINK(19) LB_LINK(20)
-                    LB_LINK(21) LB_LINK(22) LB_LINK(23) LB_LINK(24) LB_LINK(25) LB_LINK(26)
+                    LB_LINK(14) LB_LINK(15) LB_LINK(16) LB_LINK(17)
+                    sched_fence();
+                    LB_LINK(18) LB_LINK(19) LB_LINK(20) LB_LINK(21) LB_LINK(22)
+                    sched_fence();
+                    LB_LINK(23) LB_LINK(24) LB_LINK(25) LB_LINK(26)
+                    sched_fence();
 #undef LB_LINK
                 }
                 PT pnew;
                 if constexpr (ACO)
-                    pnew = rk_a * gconst((const double *)B.phin0)[own] +
+                    pnew = rk_a * at((const double *)B.phin0, z, 1, 1) +
                            rk_b * (po + ((acc[0] + acc[1]) + (acc[2] + acc[3])));
                 else
                     pnew = PS::add(po, (acc[0] + acc[1]) + (acc[2] + acc[3]));
-                gstb(phout + (size_t)z * plane, own_xy * (uint32_t)sizeof(PT), pnew, nt_rows && !ACO);
+                put((PT *)B.phout, z, pnew);
                 if constexpr (ML || ACO) {
                     // interface flags of the new phi, as the next network pass
                     // will see it (its FP32 value): one byte per 32-lane half
@@ -970,34 +1088,42 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
                                 (uint8_t)(((lane < 32 ? m : m >> 32) & 0xffffffffull) != 0);
                     }
                 }
-                po = ldg(phin + (size_t)zn * plane, own_xy * (uint32_t)sizeof(PT));
+                po = at(phin, zn, 1, 1);
             }
             // Every other load of this plane is issued before the populations of
             // the next one: loads complete in order, so waiting for a load
             // issued after the 27 prefetches would wait for them as well.
-            if constexpr (FRC && LBM) forcing_at<TW == 64>(P, ex, (uint32_t)z * ny + yrow, aext);
+            if constexpr (FRC && LBM) forcing_at<TW == 64>(P, TP ? sex[tx] : ex, (uint32_t)z * ny + yrow, aext);
             if constexpr (ML) {
                 if (sel) {  // the network output that the learned-curvature pass left here
-                    const LBM_GLOBAL float *yi = gconst((const float *)B.mlpy) + 4 * (size_t)own;
+                    const LBM_GLOBAL float *yi = gconst((const float *)B.mlpy) + 4 * (size_t)(zp(z) + srow(1) + own_v);
                     y[0] = yi[0];
                     y[1] = yi[1];
                     y[2] = yi[2];
                     y[3] = yi[3];
                 }
             }
-            if (LBM && kLatePrefetch) fetch_pops(zn);
+            if (LBM && TP) fetch_pops(zn);
         }
         if constexpr (ACO) continue;
         // surface tension: finite differences, or blended with the network
         // output that the learned-curvature pass left for the selected cells
+        PhiGrad G;
         float fs[3] = {0.f, 0.f, 0.f};
-        if constexpr (ML) {
-            if (sel)
-                surface_blend(G, P, kfd, gn, y, fs);
-            else
-                surface_fd(G, P, fs);
-        } else if constexpr (TP) {
-            surface_fd(G, P, fs);
+        if constexpr (TP) {
+            const float4 g = sg[z & 1][tid];
+            G.phi = sphi[ring(z)][lc];
+            G.g[0] = g.x;
+            G.g[1] = g.y;
+            G.g[2] = g.z;
+            const float c = ML ? cs : g.w;
+#pragma unroll
+            for (int a = 0; a < 3; a++) fs[a] = c * G.g[a];
+            if constexpr (ML) {
+                if (sel) surface_blend(G, cs, P, g.w, grad_norm(G), y, fs);
+                cs = csn;
+                sel = seln;
+            }
         }
         {
             // moments -> forces, velocity
@@ -1007,26 +1133,20 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
             // regularised collision, written to this site's own slots
             float h[27];
             collide(m, m.omega, h);
-            const __amdgpu_buffer_rsrc_t dst = plane_rsrc(fout + (size_t)z * pstride, pbytes);
-            auto store_pops = [&](auto aux) {
-                uint32_t soff = 0;
+            const __amdgpu_buffer_rsrc_t dst = plane_rsrc(fout + (size_t)zp(z) * 27, pbytes);
+            uint32_t soff = srow(1) * ES;
 #pragma unroll
-                for (int i = 0; i < 27; i++) {
-                    bstore<T, decltype(aux)::value>(dst, own_xy * ES, soff,
-                                                    Pop<S>::enc_step(h[i], __builtin_bit_cast(uint32_t, h[(i + 1) % 27])));
-                    soff += plane * ES;
-                    asm volatile("" : "+s"(soff));
-                }
-            };
-            if (nt_rows)
-                store_pops(std::integral_constant<int, STORE_NT>{});
-            else
-                store_pops(std::integral_constant<int, 0>{});
+            for (int i = 0; i < 27; i++) {
+                bstore<T, NT ? STORE_NT : 0>(dst, own_v * ES, soff,
+                                             Pop<S>::enc_step(h[i], __builtin_bit_cast(uint32_t, h[(i + 1) % 27])));
+                soff += pstep;
+                asm volatile("" : "+s"(soff));
+            }
 
             if constexpr (TP) {  // velocity of this step, advects phi in the next one
-                gstb(uout + (size_t)z * plane, own_xy * 4u, m.u[0], nt_rows);
-                gstb(uout + (size_t)N + (size_t)z * plane, own_xy * 4u, m.u[1], nt_rows);
-                gstb(uout + 2 * (size_t)N + (size_t)z * plane, own_xy * 4u, m.u[2], nt_rows);
+                put(B.uout, z, m.u[0]);
+                put(B.uout + N, z, m.u[1]);
+                put(B.uout + 2 * (size_t)N, z, m.u[2]);
             }
         }
     }
@@ -1115,7 +1235,7 @@ __device__ __forceinline__ void pass_tile(const Params &P, const Buffers &B, con
     // for exactly the set it stores
     PT ra[LOADS], rb[LOADS], rc[LOADS];
     auto fetch_plane = [&](PT(&r)[LOADS], int z) {
-        const LBM_GLOBAL PT *src = phin + (size_t)modi(z, nz) * plane;
+        const LBM_GLOBAL PT *src = phin + (uint32_t)wrapi(z, nz) * plane;
 #pragma unroll
         for (int k = 0; k < LOADS; k++) {
             const int e = tid + k * NTHREADS;
@@ -1151,7 +1271,8 @@ __device__ __forceinline__ void pass_tile(const Params &P, const Buffers &B, con
             }
             PhiGrad G;
             float kfd, gn;
-            phi_stencil(ph, G);
+            M10 M;
+            phi_stencil(ph, M, G);
             sel = mlp_select(G, P, kfd, gn);
         }
         mlp_wave(W, wave_lds[tid >> 6], sel, ph, y, tid & 63);
@@ -1203,6 +1324,11 @@ __device__ __forceinline__ void pass_tile(const Params &P, const Buffers &B, con
 // third (FP16) but made the FP32 step 2.5 % slower and left FP16 unchanged: the
 // step is not bound by the L2-miss traffic, and one queue keeps all dies on the
 // same z range.)
+// A workgroup's first item is its own index in the grid, the queue hands out
+// the items after those, and a launch of no more items than workgroups does
+// without it: the atomic additions of a whole grid on one counter take about
+// 10 ns each (a single-phase step of an 8^3 box, 1792 resident workgroups,
+// 26 us).
 template <int TW, class Body>
 __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ first, int nbox, uint32_t *counter,
                                            int parity, Body body)
@@ -1211,12 +1337,7 @@ __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ first, i
     const int tid = threadIdx.y * TW + threadIdx.x;
     const uint32_t total = first[nbox];
     if (blockIdx.x == 0 && tid == 0) counter[parity ^ 1] = 0u;
-    for (;;) {
-        if (tid == 0) s_item = atomicAdd(&counter[parity], 1u);
-        __syncthreads();
-        const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane(s_item);
-        __syncthreads();  // s_item read by all; the previous item's LDS traffic is over
-        if (item >= total) break;
+    for (uint32_t item = blockIdx.x; item < total;) {
         int lo = 0, hi = nbox - 1;  // last box with first[b] <= item
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1225,6 +1346,11 @@ __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ first, i
         }
         const int b = __builtin_amdgcn_readfirstlane(lo);
         body(b, item - first[b]);
+        if (total <= gridDim.x) break;
+        if (tid == 0) s_item = gridDim.x + atomicAdd(&counter[parity], 1u);
+        __syncthreads();  // the item's LDS traffic is over
+        item = (uint32_t)__builtin_amdgcn_readfirstlane(s_item);
+        __syncthreads();  // s_item read by all
     }
 }
 
@@ -1237,7 +1363,7 @@ k_ac_stage_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf
                  int nbox, uint32_t *counter, int parity, double rk_a, double rk_b)
 {
     batch_loop<TW>(first, nbox, counter, parity, [&](int b, uint32_t L) {
-        step_tile<0, true, false, false, TW, true, false, true>(tab[b], buf[b], L, rk_a, rk_b);
+        step_tile<0, true, false, false, TW, false, false, true>(tab[b], buf[b], L, rk_a, rk_b);
     });
 }
 
@@ -1260,13 +1386,13 @@ k_mlp_pass_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf
 // The time step of one or many independent boxes in one launch (a single box
 // is a batch of one); tab[b] and buf[b] are the box's parameters and this
 // step's buffers.
-template <int S, bool TP, bool FRC, bool ML, int TW, bool FX, bool PH>
+template <int S, bool TP, bool FRC, bool ML, int TW, bool FX, bool PH, bool NT>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3)))
 k_step_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf, const uint32_t *__restrict__ first,
              int nbox, uint32_t *counter, int parity)
 {
     batch_loop<TW>(first, nbox, counter, parity, [&](int b, uint32_t L) {
-        step_tile<S, TP, FRC, ML, TW, true, FX, false, PH>(tab[b], buf[b], L);
+        step_tile<S, TP, FRC, ML, TW, NT, FX, false, PH>(tab[b], buf[b], L);
     });
 }
 
@@ -1289,6 +1415,10 @@ k_step_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf, co
         else LBM_DISPATCH_S(2, tp, frc, ml, CALL);                             \
     } while (0)
 
+// Non-temporal stores are a template parameter: chosen at run time inside the
+// kernel, the two store sequences made the compiler's counting of the
+// operations in flight lose the 27 stores, and every plane then waited for the
+// previous plane's stores before it used its populations.
 // the step kernel also takes the phi storage and whether buoyancy or a
 // viscosity contrast is compiled in (both exist only with the phase field)
 #define LBM_STEP_CALL(S_, TP_, F_, M_)                                                               \
@@ -1306,42 +1436,38 @@ k_step_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf, co
 // Occupancy-sized persistent grid and launch of the step kernel for one
 // population storage S; each storage is instantiated in a translation unit
 // of its own (lbm_step_s0/s1/s2.hip) so that the build compiles them in parallel.
+// nt: non-temporal stores (tile 64 only)
+#define LBM_STEP_TILE(S_, TP_, F_, M_, X_, H_, CALL)                                   \
+    {                                                                                  \
+        if (tile == 32) CALL((k_step_batch<S_, TP_, F_, M_, 32, X_, H_, false>))       \
+        else if (nt) CALL((k_step_batch<S_, TP_, F_, M_, 64, X_, H_, true>))           \
+        else CALL((k_step_batch<S_, TP_, F_, M_, 64, X_, H_, false>))                  \
+    }
 template <int S>
-int step_grid(bool tp, bool frc, bool ml, bool fix, bool phys, int tile)
+int step_grid(bool tp, bool frc, bool ml, bool fix, bool phys, int tile, bool nt)
 {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-#define STEP_CALL(S_, TP_, F_, M_, X_, H_)                                                                         \
-    {                                                                                                          \
-        if (tile == 32)                                                                                        \
-            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step_batch<S_, TP_, F_, M_, 32, X_, H_>,  \
-                                                               NTHREADS, 0);                                   \
-        else                                                                                                   \
-            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step_batch<S_, TP_, F_, M_, 64, X_, H_>,  \
-                                                               NTHREADS, 0);                                   \
-    }
+#define STEP_GRID(K) (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, K, NTHREADS, 0);
+#define STEP_CALL(S_, TP_, F_, M_, X_, H_) LBM_STEP_TILE(S_, TP_, F_, M_, X_, H_, STEP_GRID)
     LBM_DISPATCH_S(S, tp, frc, ml, LBM_STEP_CALL);
 #undef STEP_CALL
+#undef STEP_GRID
     return per_cu * cus;
 }
 
 template <int S>
 hipError_t step_launch(const Params *tab, const Buffers *buf, const uint32_t *first, int nbox, uint32_t *counter,
-                       int parity, bool tp, bool frc, bool ml, bool fix, bool phys, int tile, int grid, hipStream_t s)
+                       int parity, bool tp, bool frc, bool ml, bool fix, bool phys, int tile, bool nt, int grid,
+                       hipStream_t s)
 {
     dim3 g(grid), block(tile, NTHREADS / tile, 1);
-#define STEP_CALL(S_, TP_, F_, M_, X_, H_)                                                                         \
-    {                                                                                                          \
-        if (tile == 32)                                                                                        \
-            hipLaunchKernelGGL((k_step_batch<S_, TP_, F_, M_, 32, X_, H_>), g, block, 0, s, tab, buf, first, nbox,  \
-                               counter, parity);                                                               \
-        else                                                                                                   \
-            hipLaunchKernelGGL((k_step_batch<S_, TP_, F_, M_, 64, X_, H_>), g, block, 0, s, tab, buf, first, nbox,  \
-                               counter, parity);                                                               \
-    }
+#define STEP_LAUNCH(K) hipLaunchKernelGGL(K, g, block, 0, s, tab, buf, first, nbox, counter, parity);
+#define STEP_CALL(S_, TP_, F_, M_, X_, H_) LBM_STEP_TILE(S_, TP_, F_, M_, X_, H_, STEP_LAUNCH)
     LBM_DISPATCH_S(S, tp, frc, ml, LBM_STEP_CALL);
 #undef STEP_CALL
+#undef STEP_LAUNCH
     return hipGetLastError();
 }
 

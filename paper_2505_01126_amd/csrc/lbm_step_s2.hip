@@ -3,8 +3,8 @@
 
 namespace lbm {
 
-template int step_grid<2>(bool, bool, bool, bool, bool, int);
+template int step_grid<2>(bool, bool, bool, bool, bool, int, bool);
 template hipError_t step_launch<2>(const Params *, const Buffers *, const uint32_t *, int, uint32_t *, int, bool, bool,
-                                    bool, bool, bool, int, int, hipStream_t);
+                                    bool, bool, bool, int, bool, int, hipStream_t);
 
 }  // namespace lbm
