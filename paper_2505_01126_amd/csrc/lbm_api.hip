@@ -19,10 +19,6 @@
 namespace {
 
 constexpr size_t ALIGN = 256;
-// default z planes per work item: 32 for FP32 populations, 64 for 16-bit ones
-// (measured on 512^3: FP16 5.54 ms at 64 vs 5.67 at 32; FP32 equal at both)
-int default_zchunk(int storage) { return storage == LBM_STORE_F32 ? 32 : 64; }
-
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 size_t elem_bytes(int storage) { return storage == LBM_STORE_F32 ? 4 : 2; }
@@ -79,6 +75,18 @@ Layout layout_of(const lbm_config &c)
     L.self_batch = take(lbm_batch_bytes(1));  // tables of the box's own one-member batch
     L.total = off;
     return L;
+}
+
+// work decomposition of one box: tile width (64 or 32 sites in x, 256 sites
+// per tile) and z-chunk length
+void set_tiling(lbm::Params &P, int tile, int zc)
+{
+    const int ty = lbm::NTHREADS / tile;
+    P.gx = (P.nx + tile - 1) / tile;
+    P.gy = (P.ny + ty - 1) / ty;
+    P.zchunk = zc > P.nz ? P.nz : zc;
+    P.gz = (P.nz + P.zchunk - 1) / P.zchunk;
+    P.nblocks = P.gx * P.gy * P.gz;
 }
 
 const char *validate(const lbm_config *c)
@@ -140,7 +148,7 @@ struct lbm_batch {
     hipStream_t capture = nullptr;  // private stream the step-pair graph is recorded on
     char *table = nullptr;
     size_t off_tab = 0, off_buf = 0, off_first = 0, off_counter = 0;
-    int storage = 0, grid = 0, parity = 0, zchunk = 32, tile = 64;
+    int storage = 0, grid = 0, parity = 0, tile = 64;
     bool tp = false, frc = false, ml = false, fix = false, rk3 = false, phys = false, dirty = true, nt = false;
     int grid_ac = 0;  // persistent grid of the Runge-Kutta stage kernel
     int grid_ml = 0;  // persistent grid of the learned-curvature pass
@@ -254,8 +262,6 @@ int lbm_init(lbm_handle **out, const lbm_config *cfg, void *d_ws, size_t ws_byte
     P.nx = cfg->nx;
     P.ny = cfg->ny;
     P.nz = cfg->nz;
-    int zc = cfg->zchunk > 0 ? cfg->zchunk : default_zchunk(cfg->storage);
-    P.zchunk = zc > cfg->nz ? cfg->nz : zc;
     P.two_phase = cfg->two_phase;
     P.curv_mode = cfg->curv_mode;
     P.n_modes = cfg->n_modes;
@@ -284,10 +290,7 @@ int lbm_init(lbm_handle **out, const lbm_config *cfg, void *d_ws, size_t ws_byte
     P.mlp = h->ws + L.mlp;
     P.frow = nullptr;
     P.fx = nullptr;
-    P.gx = (cfg->nx + lbm::TX - 1) / lbm::TX;
-    P.gy = (cfg->ny + lbm::TY - 1) / lbm::TY;
-    P.gz = (cfg->nz + P.zchunk - 1) / P.zchunk;
-    P.nblocks = P.gx * P.gy * P.gz;
+    set_tiling(P, lbm::TX, cfg->zchunk > 0 ? cfg->zchunk : cfg->nz);  // a batch chooses its own
 
     if (cfg->n_modes > 0) {
         // body-force tables in FP64 on the host, stored as FP32: per mode,
@@ -584,18 +587,6 @@ BatchOffsets batch_offsets(int n)
     return o;
 }
 
-// work decomposition of one box: tile width (64 or 32 sites in x, 256 sites
-// per tile) and z-chunk length
-void set_tiling(lbm::Params &P, int tile, int zc)
-{
-    const int ty = lbm::NTHREADS / tile;
-    P.gx = (P.nx + tile - 1) / tile;
-    P.gy = (P.ny + ty - 1) / ty;
-    P.zchunk = zc > P.nz ? P.nz : zc;
-    P.gz = (P.nz + P.zchunk - 1) / P.zchunk;
-    P.nblocks = P.gx * P.gy * P.gz;
-}
-
 // Non-temporal stores where every row of the 64-wide tiles fills whole
 // 128-byte lines in every member, and the populations outgrow the 256 MB
 // Infinity Cache: below that the next step reads them from it (64^3 FP32: 25.5
@@ -609,6 +600,54 @@ bool nt_stores(const lbm_batch *b)
     }
     return bytes > 256e6;
 }
+
+// Tile width where none is asked for: 64 sites, or 32 (two rows per wave) where
+// that saves a fifth or more of the sites that the tiles cover past the boxes'
+// edges (96^3 single phase, FP32: 43 us against 49; nx = 150, which saves a
+// sixth: 290 us against 275).
+int default_tile(const lbm_batch *b)
+{
+    double w64 = 0.0, w32 = 0.0;
+    for (const lbm_handle *h : b->m) {
+        const double rows = (double)h->cfg.ny * h->cfg.nz;
+        w64 += rows * ((h->cfg.nx + 63) / 64 * 64);
+        w32 += rows * ((h->cfg.nx + 31) / 32 * 32);
+    }
+    return 5.0 * w32 <= 4.0 * w64 ? 32 : 64;
+}
+
+// Planes per work item where none is asked for: the length that brings the
+// launch through its rounds of resident workgroups soonest, a round costing its
+// planes and, for the phase field's prologue, about three more.  A small box is
+// cut into enough items for every compute unit (64^3 two-phase FP32: 26 us at 2
+// planes, 134 at 32; 32^3 single phase: 9 and 38); a large one keeps the
+// longest item that still runs at full rate: longer ones leave the
+// last round idle and spread the planes in flight over more of memory (512^3
+// FP32: 6.75 ms at 16 planes, 6.92 at 32; FP16: 4.61 at 32, 4.79 at 16; single
+// phase, which has no prologue: FP32 5.29 ms at 2, 5.51 at 8, FP16 3.00 at 4).
+int default_zchunk(const lbm_batch *b, int tile, int slots)
+{
+    const bool half = b->storage != LBM_STORE_F32;
+    const int lo = b->tp ? 1 : 2, hi = b->tp ? (half ? 32 : 16) : (half ? 4 : 2);
+    int best = lo;
+    double cost = 0.0;
+    for (int c = lo; c <= hi; c++) {
+        double items = 0.0;
+        for (const lbm_handle *h : b->m) {
+            lbm::Params P = h->P;
+            set_tiling(P, tile, c);
+            items += P.nblocks;
+        }
+        const double t = std::ceil(items / slots) * (c + (b->tp ? 3.0 : 1.0));
+        if (c == lo || t < cost) {
+            best = c;
+            cost = t;
+        }
+    }
+    return best;
+}
+
+int choose_tiling(lbm_batch *b, int tile, int zchunk);
 
 // Upload the parameter table, both parities of the buffer table and the
 // work-item prefix sums for the members' current state.
@@ -656,6 +695,37 @@ int batch_upload(lbm_batch *b)
     b->parity = 0;
     b->dirty = false;
     b->drop_graph();
+    return LBM_OK;
+}
+
+// Set the work decomposition: tile and zchunk, or, where they are 0, the
+// defaults (and each member's own zchunk where its configuration gives one).
+int choose_tiling(lbm_batch *b, int tile, int zchunk)
+{
+    if (tile == 0) tile = default_tile(b);
+    const bool nt = nt_stores(b);
+    const int grid = lbm::batch_grid(b->storage, b->tp, b->frc, b->ml, b->fix, b->phys, tile, nt);
+    const int grid_ac = b->rk3 ? lbm::ac_stage_grid(tile) : 1;
+    const int grid_ml = b->ml ? lbm::mlp_pass_grid(b->fix, tile) : 1;
+    if (grid <= 0 || grid_ac <= 0 || grid_ml <= 0) return b->fail(LBM_EHIP, "occupancy query failed");
+    const int zc = zchunk > 0 ? zchunk : default_zchunk(b, tile, grid);
+    for (size_t i = 0; i < b->m.size(); i++) {
+        const lbm_config &c = b->m[i]->cfg;
+        if (zchunk > 0) {
+            set_tiling(b->P[i], tile, zchunk);
+        } else if (c.zchunk > 0) {
+            set_tiling(b->P[i], tile, c.zchunk);
+        } else {  // as few items as zc gives, of even length
+            const int gz = (c.nz + zc - 1) / zc;
+            set_tiling(b->P[i], tile, (c.nz + gz - 1) / gz);
+        }
+    }
+    b->tile = tile;
+    b->nt = nt;
+    b->grid = grid;
+    b->grid_ac = grid_ac;
+    b->grid_ml = grid_ml;
+    b->dirty = true;
     return LBM_OK;
 }
 
@@ -756,11 +826,7 @@ int lbm_batch_create(lbm_batch **out, lbm_handle *const *members, int n, void *d
     b->rk3 = h0->cfg.two_phase && h0->cfg.ac_rk3;
     b->phys = h0->P.gravity_on || h0->P.tau_g > 0.0f;
     for (lbm_handle *h : m) b->P.push_back(h->P);
-    b->nt = nt_stores(b);
-    b->grid = lbm::batch_grid(b->storage, b->tp, b->frc, b->ml, b->fix, b->phys, b->tile, b->nt);
-    b->grid_ac = b->rk3 ? lbm::ac_stage_grid(b->tile) : 1;
-    b->grid_ml = b->ml ? lbm::mlp_pass_grid(b->fix, b->tile) : 1;
-    if (b->grid <= 0 || b->grid_ac <= 0 || b->grid_ml <= 0) {
+    if (choose_tiling(b, 0, 0) != LBM_OK) {
         delete b;
         return bad(LBM_EHIP, "occupancy query failed");
     }
@@ -890,18 +956,7 @@ int lbm_batch_set_tiling(lbm_batch *b, int tile, int zchunk)
     if (!b) return LBM_EINVAL;
     if (tile != 64 && tile != 32) return b->fail(LBM_EINVAL, "tile must be 64 or 32");
     if (zchunk < 1) return b->fail(LBM_EINVAL, "zchunk must be >= 1");
-    const int grid = lbm::batch_grid(b->storage, b->tp, b->frc, b->ml, b->fix, b->phys, tile, b->nt);
-    const int grid_ac = b->rk3 ? lbm::ac_stage_grid(tile) : 1;
-    const int grid_ml = b->ml ? lbm::mlp_pass_grid(b->fix, tile) : 1;
-    if (grid <= 0 || grid_ac <= 0 || grid_ml <= 0) return b->fail(LBM_EHIP, "occupancy query failed");
-    for (lbm::Params &P : b->P) set_tiling(P, tile, zchunk);
-    b->tile = tile;
-    b->zchunk = zchunk;
-    b->grid = grid;
-    b->grid_ac = grid_ac;
-    b->grid_ml = grid_ml;
-    b->dirty = true;
-    return LBM_OK;
+    return choose_tiling(b, tile, zchunk);
 }
 
 int lbm_batch_destroy(lbm_batch *b)
