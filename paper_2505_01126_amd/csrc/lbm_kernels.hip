@@ -150,11 +150,11 @@ template <int S, bool TP, bool FRC, bool ML>
 __global__ void __launch_bounds__(NTHREADS) k_moments(Params P, const void *fin, const void *phi, float *rho,
                                                       float *pr, float *u, double *phi_out)
 {
-    __shared__ char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
+    __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
     MlpW &W = *(MlpW *)mlp_raw;
     MlpWave *wv = (MlpWave *)(mlp_raw + (ML ? sizeof(MlpW) : 0));
     if constexpr (ML) {
-        load_weights((const uint16_t *)P.mlp, W, threadIdx.x, NTHREADS);
+        load_weights((const uint16_t *)P.mlp, W, threadIdx.x);
         __syncthreads();
     }
     const uint32_t N = (uint32_t)P.nx * P.ny * P.nz;
@@ -233,11 +233,11 @@ __device__ __forceinline__ void block_reduce(const double (&acc)[NRED], double (
 template <int S, bool TP, bool FRC, bool ML>
 __global__ void __launch_bounds__(NTHREADS) k_reduce(Params P, const void *fin, const void *phi, double *partials)
 {
-    __shared__ char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
+    __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
     MlpW &W = *(MlpW *)mlp_raw;
     MlpWave *wv = (MlpWave *)(mlp_raw + (ML ? sizeof(MlpW) : 0));
     if constexpr (ML) {
-        load_weights((const uint16_t *)P.mlp, W, threadIdx.x, NTHREADS);
+        load_weights((const uint16_t *)P.mlp, W, threadIdx.x);
         __syncthreads();
     }
     const uint32_t N = (uint32_t)P.nx * P.ny * P.nz;

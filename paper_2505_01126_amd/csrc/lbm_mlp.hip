@@ -35,16 +35,18 @@ __device__ __forceinline__ half8 load_x(const uint16_t *__restrict__ x, int64_t 
 __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
                                                      int64_t B, float *__restrict__ y)
 {
-    __shared__ WLds L;
-    __shared__ _Float16 hbuf[4][2][16][NH];
+    __shared__ MlpW L;
+    __shared__ __align__(16) _Float16 hbuf[4][16][HP];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    load_weights(w, L, tid, 256);
+    const int64_t ntiles = (B + 15) / 16, t0 = (int64_t)blockIdx.x * 4 + wave;
+    half8 xa = load_x(x, t0 * 16 + (lane & 15), B, lane >> 4);  // in flight while the weights are staged
+    load_weights(w, L, tid);
     __syncthreads();
-    const int64_t ntiles = (B + 15) / 16;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntiles; t += (int64_t)gridDim.x * 4) {
+    for (int64_t t = t0; t < ntiles; t += (int64_t)gridDim.x * 4) {
         const int64_t s0 = t * 16;
-        const half8 xa = load_x(x, s0 + (lane & 15), B, lane >> 4);
-        const f32x4 o = forward_tile(L, xa, hbuf[wave][0], hbuf[wave][1], lane);
+        const half8 xn = load_x(x, (t + (int64_t)gridDim.x * 4) * 16 + (lane & 15), B, lane >> 4);
+        const f32x4 o = forward_tile(L, xa, hbuf[wave], hbuf[wave], lane);
+        xa = xn;
         const int col = lane & 15, kq = lane >> 4;
         if (col < NOUT)
 #pragma unroll
@@ -61,99 +63,132 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *__restrict_
 //   d3 = 2 (y - t)               (the 1/B is applied at the end)
 //   d2 = (d3 W3) * (1 - h2^2),   d1 = (d2 W2) * (1 - h1^2)
 //   gW3 = d3^T h2, gW2 = d2^T h1, gW1 = d1^T x, gb = column sums,
-// accumulated over the block's chunks; block partials are summed in block
+// accumulated over the block's chunks; block partials are summed in a fixed
 // order by k_mlp_reduce.
+//
+// A batch of 16384 is one chunk for each of 256 workgroups, so what counts is
+// the length of the chain through one chunk, not any rate.  The C layout of an
+// MFMA holds four consecutive samples of one neuron per lane: h1, h2, d2 and
+// d1 go from there to LDS both by sample (the next layer's A operand) and, 8
+// bytes at a time, by neuron, which is what both operands of the weight
+// gradients read 16 bytes at a time (gathered from the layout by sample, sample
+// by sample, they took 128 reads of 2 bytes per lane).  gW3 = d3^T h2 keeps d3 in
+// FP32 on the FP32 MFMA; the bias gradients are one more column of ones in the
+// products.  The weights are read 16 bytes at a time.  16384 samples: 23.1 ->
+// 15.3 us.
 struct BLds {
     WLds W;
-    _Float16 x[CHUNK][KIN];
-    _Float16 h1[CHUNK][NH];
-    _Float16 h2[CHUNK][NH];
-    _Float16 d2[CHUNK][NH];
-    _Float16 d1[CHUNK][NH];
+    _Float16 h[4][16][HP];  // each wave's activations, then its d2, by sample
+    _Float16 xt[KIN][HP];   // by input or neuron, then by sample of the chunk
+    _Float16 h1t[NH][HP], h2t[NH][HP], d2t[NH][HP], d1t[NH][HP];
     float d3[CHUNK][NOUT];
+    float d3t[NOUT][CHUNK + 4];
 };
+static_assert(HP >= CHUNK && HP % 8 == 0, "a row by neuron holds the samples of a chunk");
 
-__device__ __forceinline__ half8 gather8(const _Float16 (*m)[NH], int s0, int col)
-{
-    half8 v;
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = m[s0 + j][col];
-    return v;
-}
-__device__ __forceinline__ half8 gather8x(const _Float16 (*m)[KIN], int s0, int col)
-{
-    half8 v;
-#pragma unroll
-    for (int j = 0; j < 8; j++) v[j] = m[s0 + j][col];
-    return v;
-}
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
 __global__ void __launch_bounds__(256) k_mlp_backward(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
                                                       const float *__restrict__ tgt, int64_t B,
                                                       float *__restrict__ partial)
 {
-    extern __shared__ char lds_raw[];
+    extern __shared__ __align__(16) char lds_raw[];
     BLds &S = *(BLds *)lds_raw;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, kq = lane >> 4;
-    load_weights(w, S.W, tid, 256);
-    // accumulators: wave owns neuron tile n = 16 wave .. +15 of gW2 (4 column
-    // tiles) and of gW1 (2 column tiles); gW3 / biases by thread
-    f32x4 acc2[4], acc1[2];
-#pragma unroll
-    for (int t = 0; t < 4; t++) acc2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < 2; t++) acc1[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float gw3 = 0.f, gb = 0.f, loss = 0.f;  // gw3: (o = tid/64, k = tid%64); gb: tid < 64 b1, < 128 b2, < 132 b3
-    __syncthreads();
     const int64_t nchunks = (B + CHUNK - 1) / CHUNK;
+    // inputs and targets of a chunk's 16 samples of this wave, fetched one chunk ahead
+    auto fetch = [&](int64_t c, half8 &xa, float (&t)[4]) {
+        const int64_t s0 = c * CHUNK + 16 * wave;
+        xa = load_x(x, s0 + r, B, kq);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int64_t s = s0 + 4 * kq + i;
+            t[i] = r < NOUT && s < B ? tgt[s * NOUT + r] : 0.0f;
+        }
+    };
+    half8 xa;
+    float t[4];
+    fetch(blockIdx.x, xa, t);
+    load_weights(w, S.W, tid);
+    // accumulators: wave owns neuron tile n = 16 wave .. +15 of gW2 (4 column
+    // tiles and one of ones, its bias), of gW1 (2 column tiles, input 27 the
+    // ones of its bias) and the columns 16 wave .. +15 of gW3
+    f32x4 acc2[5], acc1[2], acc3 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 5; k++) acc2[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 2; k++) acc1[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    half8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; j++) ones[j] = (_Float16)(r == 0 ? 1.0f : 0.0f);
+    float gb3 = 0.f, loss = 0.f;
+    __syncthreads();
+    float w3[4][NOUT];  // of this lane's neurons 16 nt + r
+#pragma unroll
+    for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+        for (int o = 0; o < NOUT; o++) w3[nt][o] = (float)S.W.w3[o][16 * nt + r];
     for (int64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
         const int64_t s0 = c * CHUNK + 16 * wave;
-        // forward, saving x, h1, h2 of this wave's 16 samples
-        const half8 xa = load_x(x, s0 + r, B, kq);
+        const int sw = 16 * wave + 4 * kq;  // this lane's four samples of the chunk
+        _Float16(*h)[HP] = S.h[wave];
 #pragma unroll
-        for (int j = 0; j < 8; j++) S.x[16 * wave + r][8 * kq + j] = xa[j];
-        const f32x4 y = forward_tile(S.W, xa, &S.h1[16 * wave], &S.h2[16 * wave], lane);
-        if (r < NOUT)
+        for (int j = 0; j < 8; j++) S.xt[8 * kq + j][16 * wave + r] = 8 * kq + j == NIN ? (_Float16)1.0f : xa[j];
+        _Float16 h1[16], h2[16];
+        const f32x4 y = forward_tile(S.W, xa, h, h, lane, h1, h2);
+        if (r < NOUT) {
+            f32x4 d;
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                const int64_t s = s0 + 4 * kq + i;
-                float d = 0.f;
-                if (s < B) {
-                    const float e = y[i] - tgt[s * NOUT + r];
-                    loss += e * e;
-                    d = 2.0f * e;
-                }
-                S.d3[16 * wave + 4 * kq + i][r] = d;
+                const float e = s0 + 4 * kq + i < B ? y[i] - t[i] : 0.0f;
+                loss += e * e;
+                d[i] = 2.0f * e;
+                S.d3[sw + i][r] = d[i];
             }
-        __syncthreads();
-        // d2 = (d3 W3) (1 - h2^2): thread -> sample tid / 4, 16 neurons
+            *(f32x4 *)&S.d3t[r][sw] = d;
+        }
+        fetch(c + gridDim.x, xa, t);
+        wave_lds_sync();
+        // d2 in the C layout of h2
         {
-            const int s = tid >> 2, k0 = (tid & 3) * 16;
+            f32x4 d3[4];
 #pragma unroll
-            for (int k = k0; k < k0 + 16; k++) {
-                float v = 0.f;
+            for (int i = 0; i < 4; i++) d3[i] = *(const f32x4 *)&S.d3[sw + i][0];
 #pragma unroll
-                for (int o = 0; o < NOUT; o++) v += S.d3[s][o] * (float)S.W.w3[o][k];
-                const float h = (float)S.h2[s][k];
-                S.d2[s][k] = (_Float16)(v * (1.0f - h * h));
+            for (int nt = 0; nt < 4; nt++) {
+                half4 v2, a1, a2;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    float v = 0.f;
+#pragma unroll
+                    for (int o = 0; o < NOUT; o++) v += d3[i][o] * w3[nt][o];
+                    const float hv = (float)h2[4 * nt + i];
+                    v2[i] = (_Float16)(v * (1.0f - hv * hv));
+                    a1[i] = h1[4 * nt + i];
+                    a2[i] = h2[4 * nt + i];
+                    h[4 * kq + i][16 * nt + r] = v2[i];
+                }
+                *(half4 *)&S.h1t[16 * nt + r][sw] = a1;
+                *(half4 *)&S.h2t[16 * nt + r][sw] = a2;
+                *(half4 *)&S.d2t[16 * nt + r][sw] = v2;
             }
         }
-        __syncthreads();
-        // d1 = (d2 W2) (1 - h1^2) on MFMA: wave's 16 samples, 4 column tiles
+        wave_lds_sync();
+        // d1 = (d2 W2) (1 - h1^2)
         {
-            const int sw = 16 * wave;
-            const half8 a0 = ld8(&S.d2[sw + r][8 * kq]), a1 = ld8(&S.d2[sw + r][32 + 8 * kq]);
+            const half8 a0 = ld8(&h[r][8 * kq]), a1 = ld8(&h[r][32 + 8 * kq]);
 #pragma unroll
             for (int nt = 0; nt < 4; nt++) {
                 f32x4 cc = {0.f, 0.f, 0.f, 0.f};
                 cc = mfma(a0, ld8(&S.W.w2t[16 * nt + r][8 * kq]), cc);
                 cc = mfma(a1, ld8(&S.W.w2t[16 * nt + r][32 + 8 * kq]), cc);
+                half4 v1;
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const int s = sw + 4 * kq + i, k = 16 * nt + r;
-                    const float h = (float)S.h1[s][k];
-                    S.d1[s][k] = (_Float16)(cc[i] * (1.0f - h * h));
+                    const float hv = (float)h1[4 * nt + i];
+                    v1[i] = (_Float16)(cc[i] * (1.0f - hv * hv));
                 }
+                *(half4 *)&S.d1t[16 * nt + r][sw] = v1;
             }
         }
         __syncthreads();
@@ -163,21 +198,26 @@ __global__ void __launch_bounds__(256) k_mlp_backward(const uint16_t *__restrict
 #pragma unroll
             for (int ks = 0; ks < 2; ks++) {
                 const int sb = 32 * ks + 8 * kq;
-                const half8 a2 = gather8(S.d2, sb, n);
-                const half8 a1 = gather8(S.d1, sb, n);
+                const half8 a2 = ld8(&S.d2t[n][sb]), a1 = ld8(&S.d1t[n][sb]);
 #pragma unroll
-                for (int nt = 0; nt < 4; nt++) acc2[nt] = mfma(a2, gather8(S.h1, sb, 16 * nt + r), acc2[nt]);
+                for (int nt = 0; nt < 4; nt++) acc2[nt] = mfma(a2, ld8(&S.h1t[16 * nt + r][sb]), acc2[nt]);
+                acc2[4] = mfma(a2, ones, acc2[4]);
 #pragma unroll
-                for (int nt = 0; nt < 2; nt++) acc1[nt] = mfma(a1, gather8x(S.x, sb, 16 * nt + r), acc1[nt]);
+                for (int nt = 0; nt < 2; nt++) acc1[nt] = mfma(a1, ld8(&S.xt[16 * nt + r][sb]), acc1[nt]);
             }
-            const int o = tid >> 6, k = tid & 63;
-            for (int s = 0; s < CHUNK; s++) gw3 += S.d3[s][o] * (float)S.h2[s][k];
-            if (tid < 64) {
-                for (int s = 0; s < CHUNK; s++) gb += (float)S.d1[s][tid];
-            } else if (tid < 128) {
-                for (int s = 0; s < CHUNK; s++) gb += (float)S.d2[s][tid - 64];
-            } else if (tid < 128 + NOUT) {
-                for (int s = 0; s < CHUNK; s++) gb += S.d3[s][tid - 128];
+            // FP32 MFMA 16x16x4 (A: row l % 16, k = l / 16; B: column l % 16,
+            // k = l / 16; C as above): step j takes sample 16 (l / 16) + j, so
+            // that a lane reads its operands of all steps contiguously
+            f32x4 a[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                a[q] = r < NOUT ? *(const f32x4 *)&S.d3t[r][16 * kq + 4 * q] : f32x4{0.f, 0.f, 0.f, 0.f};
+            const half8 b0 = ld8(&S.h2t[n][16 * kq]), b1 = ld8(&S.h2t[n][16 * kq + 8]);
+#pragma unroll
+            for (int j = 0; j < 16; j++) {
+                const float av = a[j / 4][j % 4];
+                acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, (float)(j < 8 ? b0[j % 8] : b1[j % 8]), acc3, 0, 0, 0);
+                gb3 += av;
             }
         }
         __syncthreads();
@@ -185,43 +225,66 @@ __global__ void __launch_bounds__(256) k_mlp_backward(const uint16_t *__restrict
     // block partial: [NPARAM + 1] floats (gradient, then the loss)
     float *P = partial + (size_t)blockIdx.x * (NPARAM + 1);
     {
-        const int n0 = 16 * wave;
+        const int n0 = 16 * wave + 4 * kq;
 #pragma unroll
         for (int nt = 0; nt < 4; nt++)
 #pragma unroll
-            for (int i = 0; i < 4; i++) P[OW2 + (n0 + 4 * kq + i) * NH + 16 * nt + r] = acc2[nt][i];
+            for (int i = 0; i < 4; i++) P[OW2 + (n0 + i) * NH + 16 * nt + r] = acc2[nt][i];
 #pragma unroll
         for (int nt = 0; nt < 2; nt++)
 #pragma unroll
             for (int i = 0; i < 4; i++) {
                 const int k = 16 * nt + r;
-                if (k < NIN) P[OW1 + (n0 + 4 * kq + i) * NIN + k] = acc1[nt][i];
+                if (k < NIN) P[OW1 + (n0 + i) * NIN + k] = acc1[nt][i];
+                else if (k == NIN) P[OB1 + n0 + i] = acc1[nt][i];
             }
-        P[OW3 + (tid >> 6) * NH + (tid & 63)] = gw3;
-        if (tid < 64) P[OB1 + tid] = gb;
-        else if (tid < 128) P[OB2 + tid - 64] = gb;
-        else if (tid < 128 + NOUT) P[OB3 + tid - 128] = gb;
+        if (r == 0)
+#pragma unroll
+            for (int i = 0; i < 4; i++) P[OB2 + n0 + i] = acc2[4][i];
+        if (kq == 0)
+#pragma unroll
+            for (int i = 0; i < 4; i++) P[OW3 + i * NH + 16 * wave + r] = acc3[i];
+        gb3 += __shfl_xor(gb3, 16, 64);
+        gb3 += __shfl_xor(gb3, 32, 64);
+        if (wave == 0 && lane < NOUT) P[OB3 + lane] = gb3;
     }
     // loss: fixed-order sum over the lanes that hold outputs
-    __shared__ float lsum[256];
-    lsum[tid] = loss;
+    __shared__ float lsum[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
+    if (lane == 0) lsum[wave] = loss;
     __syncthreads();
-    if (tid == 0) {
-        float s = 0.f;
-        for (int t = 0; t < 256; t++) s += lsum[t];
-        P[NPARAM] = s;
-    }
+    if (tid == 0) P[NPARAM] = (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
 }
 
-__global__ void __launch_bounds__(256) k_mlp_reduce(const float *__restrict__ partial, int nblocks, float inv_b,
-                                                    float *__restrict__ grad, float *__restrict__ loss)
+// Sums of the block partials: 32 values per workgroup, 16 threads to a value,
+// each every 16th partial, then a tree in a fixed order.  Bound by the latency
+// of its loads (6.4 MB for 256 partials): one thread per value, adding them one
+// after the other, took 58.7 us, this 4.9 us.
+constexpr int RED_VALS = 32, RED_THREADS = 16;
+__global__ void __launch_bounds__(RED_VALS *RED_THREADS)
+    k_mlp_reduce(const float *__restrict__ partial, int nblocks, float inv_b, float *__restrict__ grad,
+                 float *__restrict__ loss)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p > NPARAM) return;
-    float s = 0.f;
-    for (int b = 0; b < nblocks; b++) s += partial[(size_t)b * (NPARAM + 1) + p];
-    if (p < NPARAM) grad[p] = s * inv_b;
-    else loss[0] = s * inv_b;
+    __shared__ float sum[RED_THREADS][RED_VALS];
+    const int v = threadIdx.x % RED_VALS, g = threadIdx.x / RED_VALS, p = blockIdx.x * RED_VALS + v;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (p <= NPARAM) {
+        int b = g;
+        for (; b + 3 * RED_THREADS < nblocks; b += 4 * RED_THREADS)
+#pragma unroll
+            for (int k = 0; k < 4; k++) s[k] += partial[(size_t)(b + k * RED_THREADS) * (NPARAM + 1) + p];
+        for (int k = 0; b < nblocks; b += RED_THREADS, k++) s[k] += partial[(size_t)b * (NPARAM + 1) + p];
+    }
+    sum[g][v] = (s[0] + s[1]) + (s[2] + s[3]);
+#pragma unroll
+    for (int h = RED_THREADS / 2; h > 0; h /= 2) {
+        __syncthreads();
+        if (g < h) sum[g][v] += sum[g + h][v];
+    }
+    if (g != 0 || p > NPARAM) return;
+    if (p < NPARAM) grad[p] = sum[0][v] * inv_b;
+    else loss[0] = sum[0][v] * inv_b;
 }
 
 // ----------------------------------------------------------------- Adam
@@ -361,8 +424,8 @@ hipError_t launch_mlp_backward(const uint16_t *w, const uint16_t *x, const float
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float inv_b = B > 0 ? 1.0f / (float)B : 0.0f;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 1 + 255) / 256), dim3(256), 0, s, partial, blocks, inv_b, grad,
-                       loss);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + RED_VALS) / RED_VALS), dim3(RED_VALS * RED_THREADS), 0, s,
+                       partial, blocks, inv_b, grad, loss);
     return hipGetLastError();
 }
 

@@ -1214,7 +1214,7 @@ __device__ __forceinline__ void pass_tile(const Params &P, const Buffers &B, con
         ze = z0 + s_kmax + 1;
     }
     if (P.mlp != loaded) {  // uniform: one box per work item
-        load_weights(gconst((const uint16_t *)P.mlp), W, tid, NTHREADS);
+        load_weights(gconst((const uint16_t *)P.mlp), W, tid);
         loaded = P.mlp;
     }
     const LBM_GLOBAL PT *__restrict__ phin = gconst((const PT *)B.phin);
