@@ -16,139 +16,346 @@ extern template hipError_t step_launch<1>(const Params *, const Buffers *, const
 extern template hipError_t step_launch<2>(const Params *, const Buffers *, const uint32_t *, int, uint32_t *, int, bool,
                                           bool, bool, bool, bool, int, bool, int, hipStream_t);
 
+// ------------------------------------------------------------- row marches
+// The kernels below walk a box as the step does: a workgroup takes 256 sites of
+// a plane through a chunk of z planes, one site per lane, so that the sums over a
+// plane of a stencil are formed once and carried to the two planes above, and
+// the addresses are 32-bit offsets in one plane (a thread per site, gathering
+// its whole stencil through 64-bit addresses, spent its time on those: 624
+// vector instructions per site in the FP16 read-out, and 27 phi loads).
+//
+// wx > 0: each wave takes 64 sites of one x-row, so that rows are wave-uniform
+// (scalar offsets), and wx waves stand side by side in x: the lines that a
+// shifted row of populations shares with the next 64 sites are then fetched
+// once (single-phase FP16 reduction at 256^3: 197 us with four side by side, 249
+// with four rows of 64).  With the phase field and 16-bit populations the waves
+// take four rows instead, which then share their phi rows (512^3 FP16 read-out:
+// 2.62 ms against 2.77).  Lanes past the box's edge repeat a periodic image and
+// its writes (the same bits), so that no memory operation is conditional and the
+// compiler counts those in flight exactly.
+// wx = 0: 256 consecutive sites of the plane, where rows of 64 would leave more
+// than a tenth of the lanes idle (72^3 FP32 read-out: 13 us against 24), and in
+// boxes too small for chunks of three planes on every compute unit.
+inline int march_wx(const Params &p, bool rows)
+{
+    auto fits = [&](int w) { return (p.nx + w - 1) / w * w * 10 <= p.nx * 11; };
+    if (!fits(64) || (int64_t)p.nx * p.ny * p.nz < (int64_t)NTHREADS * 6 * RED_BLOCKS) return 0;
+    return rows || !fits(128) ? 1 : (fits(256) ? 4 : 2);
+}
+template <bool ROW> struct RowMarch {
+    int nx, ny, nz, y, z0, zend;
+    uint32_t plane, xs[3], ys[3];  // periodic neighbours' columns and row offsets (k = 1 + offset)
+    bool in_row, in_box;           // the wave has sites of the box; so has the lane
+    __device__ __forceinline__ RowMarch(const Params &P, uint32_t L, int chunk, int wx)
+    {
+        nx = P.nx;
+        ny = P.ny;
+        nz = P.nz;
+        plane = (uint32_t)nx * (uint32_t)ny;
+        int x;
+        if constexpr (ROW) {
+            const int wy = 4 / wx, wave = (int)(threadIdx.x >> 6);
+            const uint32_t gx = (nx + 64 * wx - 1) / (64 * wx), gy = (ny + wy - 1) / wy;
+            x = ((int)(L % gx) * wx + wave % wx) * 64 + (int)(threadIdx.x & 63);
+            y = __builtin_amdgcn_readfirstlane((int)(L / gx % gy) * wy + wave / wx);
+            z0 = (int)(L / (gx * gy)) * chunk;
+            in_row = y < ny;
+            in_box = in_row && x < nx;
+            x %= nx;
+            y = in_row ? y : 0;
+        } else {
+            const uint32_t gp = (plane + NTHREADS - 1) / NTHREADS, e = L % gp * NTHREADS + threadIdx.x;
+            z0 = (int)(L / gp) * chunk;
+            in_row = true;
+            in_box = e < plane;
+            x = (int)((in_box ? e : plane - 1) % (uint32_t)nx);
+            y = (int)((in_box ? e : plane - 1) / (uint32_t)nx);
+        }
+        zend = min(z0 + chunk, nz);
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            xs[k] = (uint32_t)wrapi(x + k - 1, nx);
+            ys[k] = (uint32_t)wrapi(y + k - 1, ny) * (uint32_t)nx;
+        }
+    }
+    __device__ __forceinline__ uint32_t srow(int ky) const { return ROW ? ys[ky] : 0u; }
+    __device__ __forceinline__ uint32_t vcol(int ky, int kx) const { return ROW ? xs[kx] : ys[ky] + xs[kx]; }
+    template <class E> __device__ __forceinline__ __amdgpu_buffer_rsrc_t field(const E *base, int z) const
+    {
+        return plane_rsrc(base + (uint32_t)z * plane, plane * (uint32_t)sizeof(E));
+    }
+    template <class E> __device__ __forceinline__ E at(const E *base, int z, int ky, int kx) const
+    {
+        return bload<E>(field(base, z), vcol(ky, kx) * (uint32_t)sizeof(E), srow(ky) * (uint32_t)sizeof(E));
+    }
+    // the nine values of plane z (periodic) around the site
+    template <class E> __device__ __forceinline__ void at9(const E *base, int z, E (&v)[9]) const
+    {
+        const __amdgpu_buffer_rsrc_t r = field(base, wrapi(z, nz));
+#pragma unroll
+        for (int i = 0; i < 9; i++)
+            v[i] = bload<E>(r, vcol(i / 3, i % 3) * (uint32_t)sizeof(E), srow(i / 3) * (uint32_t)sizeof(E));
+    }
+    // base may be null: a buffer of no bytes, whose stores the hardware drops.
+    // Non-temporal: nothing here reads the outputs (512^3 read-out 4.13 -> 4.00 ms)
+    template <class E> __device__ __forceinline__ void put(E *base, int z, E v) const
+    {
+        const uint32_t bytes = base ? plane * (uint32_t)sizeof(E) : 0u;
+        bstore<E, STORE_NT>(plane_rsrc(base ? base + (uint32_t)z * plane : base, bytes),
+                            vcol(1, 1) * (uint32_t)sizeof(E), srow(1) * (uint32_t)sizeof(E), v);
+    }
+};
+int64_t march_tiles(const Params &p, int wx)
+{
+    if (wx == 0) return ((int64_t)p.nx * p.ny + NTHREADS - 1) / NTHREADS;
+    const int wy = 4 / wx;
+    return (int64_t)((p.nx + 64 * wx - 1) / (64 * wx)) * ((p.ny + wy - 1) / wy);
+}
+// planes per workgroup: enough workgroups to fill the chip, at most `most`
+// (the chunk's first two planes of sums are extra work; without them a longer
+// chunk gains nothing)
+int march_chunk(const Params &p, int wx, int most = 16)
+{
+    const int64_t c = march_tiles(p, wx) * p.nz / (2 * RED_BLOCKS);
+    return (int)(c < 1 ? 1 : (c < most ? c : most));
+}
+uint32_t march_items(const Params &p, int chunk, int wx)
+{
+    return (uint32_t)(march_tiles(p, wx) * ((p.nz + chunk - 1) / chunk));
+}
+
 // ----------------------------------------------------------- initial state
 // f^0 = f^eq(p*0, u0) + w H : A0 / (2 c_s^4), A0 = -c_s^2 tau (grad u0 + grad u0^T),
 // written pre-shifted (slot of x - c_i) so that the first pull yields f^0 at x.
-template <int S>
+// FP64 throughout.  Each plane of u0 is loaded once, for the gradients of the
+// three planes it enters (27 loads per site instead of 81): the sums of site
+// z+1 and z+2 are under way while those of z are completed, each in the order
+// of the velocities.
+template <int S, bool ROW>
 __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *phi_out, float *u_out,
-                                                   const double *phi0, const double *u0, const double *ps0)
+                                                   const double *phi0, const double *u0, const double *ps0, int chunk,
+                                                   int wx)
 {
     using T = typename Pop<S>::T;
+    constexpr uint32_t ES = sizeof(T);
     T *fout = (T *)fout_;
-    const int nx = P.nx, ny = P.ny, nz = P.nz;
-    const uint32_t plane = (uint32_t)nx * ny, N = plane * (uint32_t)nz;
-    const uint32_t s = blockIdx.x * NTHREADS + threadIdx.x;
-    if (s >= N) return;
-    const int x = s % nx, y = (s / nx) % ny, z = s / plane;
-    auto nb = [&](int dx, int dy, int dz) {
-        return (uint32_t)wrapi(z + dz, nz) * plane + (uint32_t)wrapi(y + dy, ny) * nx + (uint32_t)wrapi(x + dx, nx);
+    const RowMarch<ROW> R(P, blockIdx.x, chunk, wx);
+    if (!R.in_row) return;
+    const uint32_t plane = R.plane;
+    const size_t N = (size_t)plane * (uint32_t)R.nz;
+    // G[b] += d_b u terms of the velocities i0 .. i0 + 8, v: u there
+    auto grad = [](auto i0, const double (&v)[9], double (&G)[3]) {
+#pragma unroll
+        for (int j = 0; j < 9; j++) {
+            constexpr int I0 = decltype(i0)::value;
+            const double t = 3.0 * WTD(I0 + j) * v[j];
+            if (CX(I0 + j)) G[0] += t * CX(I0 + j);
+            if (CY(I0 + j)) G[1] += t * CY(I0 + j);
+            if (CZ(I0 + j)) G[2] += t * CZ(I0 + j);
+        }
     };
-    double u[3] = {0, 0, 0}, G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+    using Low = std::integral_constant<int, 0>;
+    using Mid = std::integral_constant<int, 9>;
+    using Top = std::integral_constant<int, 18>;
+    double G[3][3], Gn[3][3];  // d_b u_a at z and z+1: the planes up to z
+    double u[3] = {0, 0, 0};
+#pragma unroll
+    for (int a = 0; a < 3; a++)
+        for (int b = 0; b < 3; b++) G[a][b] = Gn[a][b] = 0.0;
     if (u0) {
-        for (int a = 0; a < 3; a++) u[a] = u0[(size_t)a * N + s];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            double v[9];
+            R.at9(u0 + a * N, R.z0 - 1, v);
+            grad(Low{}, v, G[a]);
+            R.at9(u0 + a * N, R.z0, v);
+            grad(Mid{}, v, G[a]);
+            grad(Low{}, v, Gn[a]);
+            u[a] = v[4];
+        }
+    }
+    for (int z = R.z0; z < R.zend; z++) {
+        double un[3] = {0, 0, 0}, Gnn[3][3];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            for (int b = 0; b < 3; b++) Gnn[a][b] = 0.0;
+            if (u0) {
+                double v[9];
+                R.at9(u0 + a * N, z + 1, v);
+                grad(Top{}, v, G[a]);
+                grad(Mid{}, v, Gn[a]);
+                grad(Low{}, v, Gnn[a]);
+                un[a] = v[4];
+            }
+        }
+        const double ph = P.two_phase ? R.at(phi0, z, 1, 1) : 0.0;
+        double tau = 1.0 / (double)P.omega;
+        if (P.two_phase && P.tau_g > 0.0f) {  // relaxation time of the initial phase field
+            const double c = fmin(fmax(ph, 0.0), 1.0);
+            tau = c * (double)P.tau_l + (1.0 - c) * (double)P.tau_g;
+        }
+        double A[3][3];
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+            for (int b = 0; b < 3; b++) A[a][b] = -(tau / 3.0) * (G[a][b] + G[b][a]);
+        const double dp = (ps0 ? R.at(ps0, z, 1, 1) : (double)P.p0) - (double)P.p0;
+        const double u2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+        __amdgpu_buffer_rsrc_t dst[3];  // slots of z - cz: row y - cy, column x - cx of population i
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+            dst[k] = plane_rsrc(fout + (size_t)((uint32_t)wrapi(z + 1 - k, R.nz) * plane) * 27, 27u * plane * ES);
 #pragma unroll
         for (int i = 0; i < 27; i++) {
-            const uint32_t t = nb(CX(i), CY(i), CZ(i));
-            for (int a = 0; a < 3; a++) {
-                const double v = 3.0 * WTD(i) * u0[(size_t)a * N + t];  // G[a][b] = d_b u_a
-                G[a][0] += v * CX(i);
-                G[a][1] += v * CY(i);
-                G[a][2] += v * CZ(i);
+            const double c[3] = {(double)CX(i), (double)CY(i), (double)CZ(i)};
+            const double cu = c[0] * u[0] + c[1] * u[1] + c[2] * u[2];
+            double hA = 0.0;
+            for (int a = 0; a < 3; a++)
+                for (int b = 0; b < 3; b++) hA += (c[a] * c[b] - (a == b ? 1.0 / 3.0 : 0.0)) * A[a][b];
+            const double h = dp + 3.0 * cu + 4.5 * cu * cu - 1.5 * u2 + 4.5 * hA;
+            bstore<T>(dst[CZ(i) + 1], R.vcol(1 - CY(i), 1 - CX(i)) * ES, ((uint32_t)i * plane + R.srow(1 - CY(i))) * ES,
+                      Pop<S>::enc((float)h));
+        }
+        if (P.phi_fix)  // nearest point of the fixed-point grid, clamped to its range [-2, 2)
+            R.put((int32_t *)phi_out, z, (int32_t)__builtin_rint(fmin(fmax(ph * 0x1p30, -0x1p31), 0x1p31 - 1.0)));
+        else
+            R.put((double *)phi_out, z, ph);
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            R.put(u_out ? u_out + a * N : u_out, z, (float)u[a]);
+            u[a] = un[a];
+            for (int b = 0; b < 3; b++) {
+                G[a][b] = Gn[a][b];
+                Gn[a][b] = Gnn[a][b];
             }
         }
     }
-    double tau = 1.0 / (double)P.omega;
-    if (P.two_phase && P.tau_g > 0.0f) {  // relaxation time of the initial phase field
-        const double c = fmin(fmax(phi0[s], 0.0), 1.0);
-        tau = c * (double)P.tau_l + (1.0 - c) * (double)P.tau_g;
-    }
-    double A[3][3];
-    for (int a = 0; a < 3; a++)
-        for (int b = 0; b < 3; b++) A[a][b] = -(tau / 3.0) * (G[a][b] + G[b][a]);
-    const double dp = (ps0 ? ps0[s] : (double)P.p0) - (double)P.p0;
-    const double u2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-#pragma unroll
-    for (int i = 0; i < 27; i++) {
-        const double c[3] = {(double)CX(i), (double)CY(i), (double)CZ(i)};
-        const double cu = c[0] * u[0] + c[1] * u[1] + c[2] * u[2];
-        double hA = 0.0;
-        for (int a = 0; a < 3; a++)
-            for (int b = 0; b < 3; b++) hA += (c[a] * c[b] - (a == b ? 1.0 / 3.0 : 0.0)) * A[a][b];
-        const double h = dp + 3.0 * cu + 4.5 * cu * cu - 1.5 * u2 + 4.5 * hA;
-        // slot of x - c_i in the plane-major layout
-        const size_t slot = ((size_t)wrapi(z - CZ(i), nz) * 27 + i) * plane +
-                            (uint32_t)wrapi(y - CY(i), ny) * nx + (uint32_t)wrapi(x - CX(i), nx);
-        fout[slot] = Pop<S>::enc((float)h);
-    }
-    if (phi_out) {
-        const double ph = P.two_phase ? phi0[s] : 0.0;
-        if (P.phi_fix)  // nearest point of the fixed-point grid, clamped to its range [-2, 2)
-            ((int32_t *)phi_out)[s] = (int32_t)__builtin_rint(fmin(fmax(ph * 0x1p30, -0x1p31), 0x1p31 - 1.0));
-        else
-            ((double *)phi_out)[s] = ph;
-    }
-    if (u_out)
-        for (int a = 0; a < 3; a++) u_out[(size_t)a * N + s] = (float)u[a];
 }
 
 // -------------------------------------------------- fields and reductions
-// Per-site macroscopic state at time n (pull + stencils from global memory).
-// Every lane of the wave calls this together (the network stage is a
-// wave-wide MFMA); lanes with valid == false only take part in that stage.
-template <int S, bool TP, bool FRC, bool ML>
-__device__ __forceinline__ void site_state(const Params &P, const void *fin_, const void *phi, uint32_t s,
-                                           bool valid, Macro &m, const MlpW &W, MlpWave &wv, int lane)
+// Macroscopic state at time n of the sites of item L (pull + stencils from
+// global memory): use(z, state, phi, R) for each site of the box.  In the marches
+// by rows (the long ones) and without the network, the populations and the phi
+// plane of the next site are in flight while this one is worked on.  Bound by
+// memory: 512^3 read-out, FP16 4.03 -> 2.6 ms, FP32 4.46 -> 4.0 ms (4.8 TB/s);
+// reduction, FP32 4.53 -> 3.33 ms (4.7 TB/s).
+template <int S, bool TP, bool FRC, bool ML, bool FX, bool ROW, class Use>
+__device__ __forceinline__ void read_tile(const Params &P, const void *fin_, const void *phi_, uint32_t L, int chunk,
+                                          int wx, const MlpW &W, MlpWave &wv, Use use)
 {
     using T = typename Pop<S>::T;
+    using PS = PhiStore<FX>;
+    using PT = typename PS::T;
+    constexpr uint32_t ES = sizeof(T);
+    const RowMarch<ROW> R(P, L, chunk, wx);
+    if (!R.in_row) return;
     const T *fin = (const T *)fin_;
-    const int nx = P.nx, ny = P.ny, nz = P.nz;
-    const uint32_t plane = (uint32_t)nx * ny, N = plane * (uint32_t)nz;
-    const int x = s % nx, y = (s / nx) % ny, z = s / plane;
-    // the periodic neighbours' coordinates, once per site: index k = 1 + offset
-    const uint32_t xk[3] = {(uint32_t)wrapi(x - 1, nx), (uint32_t)x, (uint32_t)wrapi(x + 1, nx)};
-    const uint32_t yk[3] = {(uint32_t)wrapi(y - 1, ny) * nx, (uint32_t)y * nx, (uint32_t)wrapi(y + 1, ny) * nx};
-    const uint32_t zk[3] = {(uint32_t)wrapi(z - 1, nz), (uint32_t)z, (uint32_t)wrapi(z + 1, nz)};
-    // population i of site s + d (plane-major layout) and the phase field there
-    auto pop_at = [&](int i, int dx, int dy, int dz) {
-        return ((size_t)zk[1 + dz] * 27 + i) * plane + yk[1 + dy] + xk[1 + dx];
-    };
-    auto site_at = [&](int dx, int dy, int dz) { return zk[1 + dz] * plane + yk[1 + dy] + xk[1 + dx]; };
-    M10 M;
-    PhiGrad G;
-    float cs = 0.f;
-    float ph[27];
-    float kfd = 0.f, gn = 0.f;
-    bool sel = false;
-    if (valid) {
-        float hv[27];
+    const PT *phi = (const PT *)phi_;
+    const uint32_t plane = R.plane;
+    T hv[27];
+    auto fetch_pops = [&](int z) {
+        const int zs[3] = {wrapi(z + 1, R.nz), z, wrapi(z - 1, R.nz)};
 #pragma unroll
-        for (int i = 0; i < 27; i++) hv[i] = Pop<S>::dec(fin[pop_at(i, -CX(i), -CY(i), -CZ(i))]);
-        moments10(hv, M);
-        if constexpr (TP) {
-#pragma unroll
-            for (int i = 0; i < 27; i++) ph[i] = (float)phi_load(phi, site_at(CX(i), CY(i), CZ(i)), P.phi_fix);
-            M10 Mp;
-            phi_stencil(ph, Mp, G);
-            cs = surface_coef<ML>(Mp, G, P);
-            if constexpr (ML) sel = mlp_select(G, P, kfd, gn);
+        for (int i = 0; i < 27; i++) {
+            const __amdgpu_buffer_rsrc_t src =
+                plane_rsrc(fin + (size_t)((uint32_t)zs[CZ(i) + 1] * plane) * 27, 27u * plane * ES);
+            hv[i] = bload<T>(src, R.vcol(1 - CY(i), 1 - CX(i)) * ES, ((uint32_t)i * plane + R.srow(1 - CY(i))) * ES);
         }
-    }
-    float fs[3] = {0.f, 0.f, 0.f};
-    float yv[4] = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (ML) {
-        mlp_wave(W, wv, sel, ph, yv, lane);
-    }
+    };
+    auto f32 = [&](const PT(&r)[9], float (&v)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; i++) v[i] = PS::f32(r[i]);
+    };
+    float4 ex = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (FRC) ex = P.fx[R.xs[1]];
+    P6 pa, pb;  // plane sums of phi at z-1 and z ...
+    float ph[27];  // ... or, for the network's inputs, the three planes themselves
+    PT c = 0, r[9];
+    float v[9];
     if constexpr (TP) {
-        if (valid) {
+        PT ra[9], rb[9];
+        R.at9(phi, R.z0 - 1, ra);
+        R.at9(phi, R.z0, rb);
+        f32(ra, v);
+        plane6(v, pa);
+        if constexpr (ML)
+            for (int i = 0; i < 9; i++) ph[9 + i] = v[i];
+        f32(rb, v);
+        plane6(v, pb);
+        if constexpr (ML)
+            for (int i = 0; i < 9; i++) ph[18 + i] = v[i];
+        c = rb[4];
+    }
+    auto fetch = [&](int z) {
+        fetch_pops(z);
+        if constexpr (TP) R.at9(phi, z + 1, r);
+    };
+    constexpr bool AHEAD = ROW && !ML;
+    auto site = [&](int z, int zn) {
+        M10 M;
+        PhiGrad G;
+        float cs = 0.f, kfd = 0.f, gn = 0.f;
+        bool sel = false;
+        PT c_next = 0;
+        {
+            float hf[27];
+#pragma unroll
+            for (int i = 0; i < 27; i++) hf[i] = Pop<S>::dec(hv[i]);
+            moments10(hf, M);
+        }
+        if constexpr (TP) {
+            M10 Mp;
+            f32(r, v);
+            c_next = r[4];
+            if constexpr (ML) {
+                for (int i = 0; i < 18; i++) ph[i] = ph[9 + i];
+                for (int i = 0; i < 9; i++) ph[18 + i] = v[i];
+                moments10(ph, Mp);
+            } else {
+                P6 n;
+                plane6(v, n);
+                planes10(pa, pb, n, Mp);
+                pa = pb;
+                pb = n;
+            }
+            phi_grad(Mp, PS::f32(c), G);
+            cs = surface_coef<ML>(Mp, G, P);
+            if constexpr (ML) sel = mlp_select(G, P, kfd, gn);  // images too: they write what the owner writes
+        }
+        if constexpr (AHEAD) fetch(zn);
+        float fs[3] = {0.f, 0.f, 0.f};
+        if constexpr (TP) {
 #pragma unroll
             for (int a = 0; a < 3; a++) fs[a] = cs * G.g[a];
             if constexpr (ML) {
-                if (sel) surface_blend(G, cs, P, kfd, gn, yv, fs);
+                if (__ballot(sel)) {  // the network: a wave-wide MFMA, so every lane takes part
+                    float y[4] = {0.f, 0.f, 0.f, 0.f};
+                    mlp_wave(W, wv, sel, ph, y, threadIdx.x & 63);
+                    if (sel) surface_blend(G, cs, P, kfd, gn, y, fs);
+                }
             }
         }
-    }
-    if (valid) {
         float aext[3] = {0.f, 0.f, 0.f};
-        if constexpr (FRC) {
-            forcing_at<false>(P, P.fx[x], (uint32_t)z * ny + y, aext);
-        }
+        if constexpr (FRC) forcing_at<ROW>(P, ex, (uint32_t)z * R.ny + R.y, aext);
+        Macro m;
         site_macro<TP>(M, G, fs, aext, P, m);
+        use(z, m, FX ? (double)c * 0x1p-30 : (double)c, R);
+        c = c_next;
+    };
+    if constexpr (AHEAD) {
+        fetch(R.z0);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): exact counts in the loop, as in the step
+        for (int z = R.z0; z < R.zend; z++) site(z, z + 1 < R.zend ? z + 1 : z);
+    } else {
+        for (int z = R.z0; z < R.zend; z++) {
+            fetch(z);
+            site(z, z);
+        }
     }
 }
 
-template <int S, bool TP, bool FRC, bool ML>
-__global__ void __launch_bounds__(NTHREADS) k_moments(Params P, const void *fin, const void *phi, float *rho,
-                                                      float *pr, float *u, double *phi_out)
+template <int S, bool TP, bool FRC, bool ML, bool FX, bool ROW>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ML || !ROW ? 3 : 4)))
+k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, float *u, double *phi_out, int chunk, int wx)
 {
     __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
     MlpW &W = *(MlpW *)mlp_raw;
@@ -157,20 +364,15 @@ __global__ void __launch_bounds__(NTHREADS) k_moments(Params P, const void *fin,
         load_weights((const uint16_t *)P.mlp, W, threadIdx.x);
         __syncthreads();
     }
-    const uint32_t N = (uint32_t)P.nx * P.ny * P.nz;
-    const uint32_t s = blockIdx.x * NTHREADS + threadIdx.x;
-    const bool valid = s < N;
-    Macro m;
-    site_state<S, TP, FRC, ML>(P, fin, phi, valid ? s : 0u, valid, m, W, wv[threadIdx.x >> 6], threadIdx.x & 63);
-    if (!valid) return;
-    if (rho) rho[s] = m.rho;
-    if (pr) pr[s] = (P.p0 + m.dp) * m.rho * (1.0f / 3.0f);
-    if (u) {
-        u[s] = m.u[0];
-        u[(size_t)N + s] = m.u[1];
-        u[2 * (size_t)N + s] = m.u[2];
-    }
-    if (phi_out) phi_out[s] = TP ? phi_load(phi, s, P.phi_fix) : 0.0;
+    const size_t N = (size_t)P.nx * P.ny * P.nz;
+    read_tile<S, TP, FRC, ML, FX, ROW>(P, fin, phi, blockIdx.x, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
+                                       [&](int z, const Macro &m, double ph, const RowMarch<ROW> &R) {
+        R.put(rho, z, m.rho);
+        R.put(pr, z, (P.p0 + m.dp) * m.rho * (1.0f / 3.0f));
+#pragma unroll
+        for (int a = 0; a < 3; a++) R.put(u ? u + a * N : u, z, m.u[a]);
+        R.put(phi_out, z, TP ? ph : 0.0);
+    });
 }
 
 // Wavefront reductions in FP64: a butterfly over the 64 lanes (xor
@@ -225,13 +427,14 @@ __device__ __forceinline__ void block_reduce(const double (&acc)[NRED], double (
     }
 }
 
-// FP64 partial sums per block over a fixed grid-stride partition, combined in
+// FP64 partial sums per block over a fixed partition of the items, combined in
 // a fixed order: the result does not depend on scheduling.  With the
 // fixed-point phi, sum phi is accumulated as the integer sum of q (exact in
 // the FP64 block partials, which stay below 2^53, and in the final int64 sum),
 // so it is a function of that integer alone.
-template <int S, bool TP, bool FRC, bool ML>
-__global__ void __launch_bounds__(NTHREADS) k_reduce(Params P, const void *fin, const void *phi, double *partials)
+template <int S, bool TP, bool FRC, bool ML, bool FX, bool ROW>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3)))
+k_reduce(Params P, const void *fin, const void *phi, double *partials, uint32_t items, int chunk, int wx)
 {
     __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
     MlpW &W = *(MlpW *)mlp_raw;
@@ -240,69 +443,62 @@ __global__ void __launch_bounds__(NTHREADS) k_reduce(Params P, const void *fin, 
         load_weights((const uint16_t *)P.mlp, W, threadIdx.x);
         __syncthreads();
     }
-    const uint32_t N = (uint32_t)P.nx * P.ny * P.nz;
     double acc[NRED];
 #pragma unroll
     for (int k = 0; k < NRED; k++) acc[k] = 0.0;
-    // uniform trip count across the block (the network stage is wave-wide)
-    for (uint32_t base = blockIdx.x * NTHREADS; base < N; base += gridDim.x * NTHREADS) {
-        const uint32_t s = base + threadIdx.x;
-        const bool valid = s < N;
-        Macro m;
-        site_state<S, TP, FRC, ML>(P, fin, phi, valid ? s : 0u, valid, m, W, wv[threadIdx.x >> 6],
-                                   threadIdx.x & 63);
-        if (!valid) continue;
-        const double ph = TP ? phi_load(phi, s, P.phi_fix) : 0.0;
-        const double r = m.rho, pstar = (double)P.p0 + (double)m.dp;
-        const double ux = m.u[0], uy = m.u[1], uz = m.u[2];
-        const bool bad = !isfinite(pstar) || !isfinite(ux) || !isfinite(uy) || !isfinite(uz) || !isfinite(ph);
-        if (bad) {
-            acc[9] += 1.0;
-            continue;
-        }
-        const double u2 = ux * ux + uy * uy + uz * uz;
-        acc[0] += P.phi_fix ? ph * 0x1p30 : ph;
-        acc[1] += r;
-        acc[2] += pstar;
-        acc[3] += r * ux;
-        acc[4] += r * uy;
-        acc[5] += r * uz;
-        acc[6] += 0.5 * r * u2;
-        acc[7] = fmax(acc[7], sqrt(u2));
-        acc[8] = TP ? fmax(acc[8], fmax(ph - 1.0, fmax(-ph, 0.0))) : 0.0;
-    }
+    for (uint32_t L = blockIdx.x; L < items; L += gridDim.x)
+        read_tile<S, TP, FRC, ML, FX, ROW>(P, fin, phi, L, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
+                                           [&](int, const Macro &m, double phv, const RowMarch<ROW> &R) {
+            if (!R.in_box) return;
+            const double ph = TP ? phv : 0.0;
+            const double r = m.rho, pstar = (double)P.p0 + (double)m.dp;
+            const double ux = m.u[0], uy = m.u[1], uz = m.u[2];
+            const bool bad = !isfinite(pstar) || !isfinite(ux) || !isfinite(uy) || !isfinite(uz) || !isfinite(ph);
+            if (bad) {
+                acc[9] += 1.0;
+                return;
+            }
+            const double u2 = ux * ux + uy * uy + uz * uz;
+            acc[0] += FX ? ph * 0x1p30 : ph;
+            acc[1] += r;
+            acc[2] += pstar;
+            acc[3] += r * ux;
+            acc[4] += r * uy;
+            acc[5] += r * uz;
+            acc[6] += 0.5 * r * u2;
+            acc[7] = fmax(acc[7], u2);  // the root of the largest below
+            acc[8] = TP ? fmax(acc[8], fmax(ph - 1.0, fmax(-ph, 0.0))) : 0.0;
+        });
+    acc[7] = sqrt(acc[7]);
     __shared__ double wred[NTHREADS / 64][NRED];
     double res = 0.0;
     block_reduce(acc, wred, res);
     if (threadIdx.x < NRED) partials[(size_t)blockIdx.x * NRED + threadIdx.x] = res;
 }
 
-__global__ void __launch_bounds__(NTHREADS) k_reduce_final(const double *partials, int nblocks, int fix, double *out)
+// one wave per statistic over the RED_BLOCKS partials
+__global__ void __launch_bounds__(64 * NRED) k_reduce_final(const double *partials, int fix, double *out)
 {
-    __shared__ double wred[NTHREADS / 64][NRED];
-    __shared__ long long wq[NTHREADS / 64];
-    double acc[NRED];
-    long long q = 0;  // fixed-point phi: integer sum of q
+    const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
+    double v[RED_BLOCKS / 64];
 #pragma unroll
-    for (int k = 0; k < NRED; k++) acc[k] = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += NTHREADS) {
+    for (int j = 0; j < RED_BLOCKS / 64; j++) v[j] = partials[(size_t)(64 * j + lane) * NRED + k];
+    if (fix && k == 0) {  // fixed-point phi: integer sum of q
+        long long q = 0;
 #pragma unroll
-        for (int k = 0; k < NRED; k++) {
-            const double v = partials[(size_t)b * NRED + k];
-            acc[k] = red_is_max(k) ? fmax(acc[k], v) : acc[k] + v;
-        }
-        if (fix) q += (long long)partials[(size_t)b * NRED];
+        for (int j = 0; j < RED_BLOCKS / 64; j++) q += (long long)v[j];
+        q = wave_sum_i64(q);
+        if (lane == 0) out[0] = (double)q * 0x1p-30;
+        return;
     }
-    q = wave_sum_i64(q);
-    if ((threadIdx.x & 63) == 0) wq[threadIdx.x >> 6] = q;
-    double res = 0.0;
-    block_reduce(acc, wred, res);  // its barrier also publishes wq
-    if (threadIdx.x < NRED) {
-        long long qs = 0;
+    double s = 0.0, m = 0.0;  // the maxima are of values >= 0
 #pragma unroll
-        for (int w = 0; w < NTHREADS / 64; w++) qs += wq[w];
-        out[threadIdx.x] = (fix && threadIdx.x == 0) ? (double)qs * 0x1p-30 : res;
+    for (int j = 0; j < RED_BLOCKS / 64; j++) {
+        s += v[j];
+        m = fmax(m, v[j]);
     }
+    s = red_is_max(k) ? wave_reduce<7>(m) : wave_reduce<0>(s);
+    if (lane == 0) out[k] = s;
 }
 
 // --------------------------------------------------------------- launchers
@@ -382,39 +578,62 @@ hipError_t launch_ac_stage_batch(const Params *tab, const Buffers *buf, const ui
 hipError_t launch_init(const Params &p, int storage, void *fout, void *phi_out, float *u_out, const double *phi0,
                        const double *u0, const double *ps0, hipStream_t s)
 {
-    const uint32_t N = (uint32_t)p.nx * p.ny * p.nz;
-    dim3 grid((N + NTHREADS - 1) / NTHREADS), block(NTHREADS);
-    if (storage == 0) hipLaunchKernelGGL(k_init<0>, grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0);
-    else if (storage == 1) hipLaunchKernelGGL(k_init<1>, grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0);
-    else hipLaunchKernelGGL(k_init<2>, grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0);
+    const int wx = march_wx(p, false), c = march_chunk(p, wx);
+    dim3 grid(march_items(p, c, wx)), block(NTHREADS);
+#define INIT(S_, R_) \
+    hipLaunchKernelGGL((k_init<S_, R_>), grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0, c, wx)
+    if (wx) {
+        if (storage == 0) INIT(0, true);
+        else if (storage == 1) INIT(1, true);
+        else INIT(2, true);
+    } else {
+        if (storage == 0) INIT(0, false);
+        else if (storage == 1) INIT(1, false);
+        else INIT(2, false);
+    }
+#undef INIT
     return hipGetLastError();
 }
+
+// the read-out kernels also take the phi storage and the kind of march
+#define LBM_READ_CALL(S_, TP_, F_, M_)                                  \
+    {                                                                   \
+        if (TP_ && p.phi_fix) {                                         \
+            if (wx) READ(S_, TP_, F_, M_, TP_, true);                   \
+            else READ(S_, TP_, F_, M_, TP_, false);                     \
+        } else {                                                        \
+            if (wx) READ(S_, TP_, F_, M_, false, true);                 \
+            else READ(S_, TP_, F_, M_, false, false);                   \
+        }                                                               \
+    }
 
 hipError_t launch_moments(const Params &p, int storage, const void *fin, const void *phi, float *rho, float *pr,
                           float *u, double *phi_out, hipStream_t s)
 {
-    const uint32_t N = (uint32_t)p.nx * p.ny * p.nz;
-    dim3 grid((N + NTHREADS - 1) / NTHREADS), block(NTHREADS);
+    const int wx = march_wx(p, p.two_phase && storage != 0), c = march_chunk(p, wx, p.two_phase ? 16 : 4);
+    dim3 grid(march_items(p, c, wx)), block(NTHREADS);
     const bool tp = p.two_phase != 0, frc = p.n_modes > 0, ml = p.curv_mode == 1;
-#define CALL(S_, TP_, F_, M_) \
-    hipLaunchKernelGGL((k_moments<S_, TP_, F_, M_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out);
-    LBM_DISPATCH(storage, tp, frc, ml, CALL);
-#undef CALL
+#define READ(S_, TP_, F_, M_, X_, R_) \
+    hipLaunchKernelGGL((k_moments<S_, TP_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out, c, wx)
+    LBM_DISPATCH(storage, tp, frc, ml, LBM_READ_CALL);
+#undef READ
     return hipGetLastError();
 }
 
 hipError_t launch_reduce(const Params &p, int storage, const void *fin, const void *phi, double *partials,
                          double *out, hipStream_t s)
 {
+    const int wx = march_wx(p, p.two_phase && storage != 0), c = march_chunk(p, wx);
+    const uint32_t items = march_items(p, c, wx);
     dim3 grid(RED_BLOCKS), block(NTHREADS);
     const bool tp = p.two_phase != 0, frc = p.n_modes > 0, ml = p.curv_mode == 1;
-#define CALL(S_, TP_, F_, M_) \
-    hipLaunchKernelGGL((k_reduce<S_, TP_, F_, M_>), grid, block, 0, s, p, fin, phi, partials);
-    LBM_DISPATCH(storage, tp, frc, ml, CALL);
-#undef CALL
+#define READ(S_, TP_, F_, M_, X_, R_) \
+    hipLaunchKernelGGL((k_reduce<S_, TP_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, partials, items, c, wx)
+    LBM_DISPATCH(storage, tp, frc, ml, LBM_READ_CALL);
+#undef READ
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), block, 0, s, partials, (int)RED_BLOCKS, p.phi_fix, out);
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64 * NRED), 0, s, partials, p.phi_fix, out);
     return hipGetLastError();
 }
 
