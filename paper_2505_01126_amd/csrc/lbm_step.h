@@ -123,13 +123,6 @@ template <class T> __device__ __forceinline__ const LBM_GLOBAL T *gconst(const T
     return (const LBM_GLOBAL T *)p;
 }
 template <class T> __device__ __forceinline__ LBM_GLOBAL T *gmut(T *p) { return (LBM_GLOBAL T *)p; }
-// Element at a 32-bit byte offset from a wave-uniform base (a plane of a
-// field): the scalar-base + 32-bit vector-offset form of a global load, with
-// no 64-bit address arithmetic per lane.
-template <class T> __device__ __forceinline__ T ldg(const LBM_GLOBAL T *base, uint32_t byte_off)
-{
-    return *(const LBM_GLOBAL T *)((const LBM_GLOBAL char *)base + byte_off);
-}
 
 // Phase-field storage of the step: FP64 (fluxes summed in FP64), or int32
 // fixed point q = phi 2^30 (each flux rounded to nearest on that grid, summed
@@ -782,9 +775,9 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
     __shared__ float sjx[TP ? TL::NXF : 1];
     __shared__ float sjy[TP ? TL::NYF : 1];
     // plane sums of the halo points: each point's three sums of the last two
-    // planes and the next, read and written by its own thread only (kept in
-    // registers they made the step spill)
-    __shared__ float sh[TP ? 3 : 1][3][TP ? QHALO : 1];
+    // planes, read and written by its own thread only (kept in registers they
+    // made the step spill)
+    __shared__ float sh[TP ? 2 : 1][3][TP ? QHALO : 1];
     const int lc = (ty + HY) * PX + (tx + HX);  // own phi tile index
     PT phn[LOADS];          // prefetched phi plane
     uint32_t p_off[LOADS];  // byte offsets of its points in a plane
@@ -862,7 +855,7 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
         for (int i = 0; i < 9; i++) v[i] = p[(i / 3 - 1) * PX + i % 3 - 1];
     };
     auto put3 = [&](int z, const P3 &n) {
-        auto &h = sh[(z + 3) % 3];
+        auto &h = sh[z & 1];
         h[0][hp] = n.p00;
         h[1][hp] = n.p01;
         h[2][hp] = n.p10;
@@ -901,7 +894,7 @@ __device__ __forceinline__ void step_tile(const Params &P, const Buffers &B, con
             P3 n;
             load9(pn + h_lc, v);
             plane3(v, n);
-            const auto &a3 = sh[(z + 2) % 3], &b3 = sh[(z + 3) % 3];
+            const auto &a3 = sh[(z + 1) & 1], &b3 = sh[z & 1];
             q_of(fmaf(4.0f, b3[2][hp], n.p10 + a3[2][hp]), fmaf(4.0f, b3[1][hp], n.p01 + a3[1][hp]),
                  n.p00 - a3[0][hp], pc[h_lc], qv);
             put3(z + 1, n);
@@ -1356,9 +1349,13 @@ __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ first, i
 
 // One Runge-Kutta stage of the phase field of one or many boxes, on the same
 // work items as the step (buf[b].phin: the stage input, buf[b].phin0: phi^n,
-// buf[b].phout: the stage output).
+// buf[b].phout: the stage output).  Bound by vector issue and its latency, so
+// by the waves per SIMD: four fit (107 registers, 40,608 bytes of LDS per
+// workgroup with two planes of halo sums instead of three) where three did, and
+// a 256^3 time step of two stages, step and network passes went from 1.72 to
+// 1.65 ms.
 template <int TW>
-__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(4)))
 k_ac_stage_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf, const uint32_t *__restrict__ first,
                  int nbox, uint32_t *counter, int parity, double rk_a, double rk_b)
 {
