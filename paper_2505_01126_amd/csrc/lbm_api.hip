@@ -493,37 +493,29 @@ int lbm_harvest(lbm_handle *h, const double *centers, const double *radii, int n
         return LBM_EINVAL;
     if (!h->cfg.two_phase) return h->fail(LBM_ESTATE, "harvest needs a two-phase handle");
     const uint32_t N = (uint32_t)h->cfg.nx * h->cfg.ny * h->cfg.nz;
-    const int blocks = (int)std::min<uint32_t>((N + 255) / 256, lbm::HARVEST_BLOCKS);
-    const uint32_t chunk = ((N + blocks - 1) / blocks + 255) / 256 * 256;
-    std::vector<double> sph(4 * (size_t)std::max(nb, 1), 0.0);
-    for (int k = 0; k < nb; k++) {
-        sph[4 * k + 0] = centers[3 * k + 0];
-        sph[4 * k + 1] = centers[3 * k + 1];
-        sph[4 * k + 2] = centers[3 * k + 2];
-        sph[4 * k + 3] = radii[k];
-    }
+    const uint32_t chunk = ((N + lbm::HARVEST_BLOCKS - 1) / lbm::HARVEST_BLOCKS + 63) / 64 * 64;
+    const int blocks = (int)((N + chunk - 1) / chunk);
+    lbm::SphereArgs few{};
+    std::vector<lbm::Sphere> many(nb > lbm::ARG_SPHERES ? nb : 0);
+    lbm::Sphere *sph = many.empty() ? few.s : many.data();
+    for (int k = 0; k < nb; k++) sph[k] = {centers[3 * k + 0], centers[3 * k + 1], centers[3 * k + 2], radii[k]};
     long long *counts = (long long *)(h->ws + h->L.hcount);
-    long long *offsets = counts + lbm::HARVEST_BLOCKS;
-    std::vector<long long> hc(blocks), ho(blocks);
+    long long *d_total = counts + lbm::HARVEST_BLOCKS;
+    lbm::Sphere *d_sph = many.empty() ? nullptr : (lbm::Sphere *)(h->ws + h->L.sph);
     const void *phi = h->phi(h->cur);
-    hipError_t e = hipMemcpyAsync(h->ws + h->L.sph, sph.data(), sizeof(double) * 4 * nb, hipMemcpyHostToDevice,
-                                  h->stream);
+    long long total = 0;
+    hipError_t e = hipSuccess;
+    if (d_sph)
+        e = hipMemcpyAsync(d_sph, many.data(), sizeof(lbm::Sphere) * nb, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = lbm::launch_harvest_count(phi, h->P.phi_fix, N, chunk, blocks, counts, h->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(hc.data(), counts, sizeof(long long) * blocks, hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) return h->hip(e, "harvest count");
-    long long total = 0;
-    for (int b = 0; b < blocks; b++) {
-        ho[b] = total;
-        total += hc[b];
-    }
-    e = hipMemcpyAsync(offsets, ho.data(), sizeof(long long) * blocks, hipMemcpyHostToDevice, h->stream);
-    if (e == hipSuccess && cap > 0)
-        e = lbm::launch_harvest_write(h->P, phi, chunk, blocks, offsets, h->ws + h->L.sph, nb, d_x, d_y, cap,
+        e = lbm::launch_harvest_write(h->P, phi, chunk, blocks, counts, d_total, few, d_sph, nb, d_x, d_y, cap,
                                       h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) return h->hip(e, "harvest write");
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&total, d_total, sizeof(long long), hipMemcpyDeviceToHost, h->stream);
+    const hipError_t w = hipStreamSynchronize(h->stream);  // total and the spheres live on this frame
+    if (e == hipSuccess) e = w;
+    if (e != hipSuccess) return h->hip(e, "harvest");
     *n_out = total;
     return LBM_OK;
 }

@@ -105,6 +105,15 @@ hipError_t launch_moments(const Params &p, int storage, const void *fin, const v
                           float *u, double *phi_out, hipStream_t s);
 constexpr int HARVEST_BLOCKS = 1024;
 constexpr int MAX_SPHERES = 1024;
+// spheres of a harvest: up to ARG_SPHERES travel as a kernel argument (1 KB of
+// the 4 KB a launch may carry) instead of through a copy to the device
+struct Sphere {
+    double x, y, z, r;
+};
+constexpr int ARG_SPHERES = 32;
+struct SphereArgs {
+    Sphere s[ARG_SPHERES];
+};
 int mlp_backward_blocks(int64_t B);
 hipError_t launch_mlp_forward(const uint16_t *w, const uint16_t *x, int64_t B, float *y, hipStream_t s);
 hipError_t launch_mlp_backward(const uint16_t *w, const uint16_t *x, const float *t, int64_t B, float *grad,
@@ -114,8 +123,8 @@ hipError_t launch_mlp_adam(float *w, float *m, float *v, const float *g, uint16_
 hipError_t launch_harvest_count(const void *phi, int fix, uint32_t N, uint32_t chunk, int blocks, long long *counts,
                                 hipStream_t s);
 hipError_t launch_harvest_write(const Params &p, const void *phi, uint32_t chunk, int blocks,
-                                const long long *offsets, const void *sph, int nb, uint16_t *X, float *Y, int64_t cap,
-                                hipStream_t s);
+                                const long long *counts, long long *total, const SphereArgs &few, const Sphere *many,
+                                int nb, uint16_t *X, float *Y, int64_t cap, hipStream_t s);
 hipError_t launch_reduce(const Params &p, int storage, const void *fin, const void *phi, double *partials,
                          double *out, hipStream_t s);
 

@@ -306,8 +306,16 @@ __global__ void __launch_bounds__(256) k_mlp_adam(float *__restrict__ w, float *
 
 // -------------------------------------------------------------- harvest
 // Interface cells (0.02 < phi < 0.98) in site order: pass 1 counts them per
-// workgroup range, the host scans the counts, pass 2 writes rows at
-// offset + rank within the range (workgroup prefix over waves).
+// workgroup range, pass 2 sums the counts of the ranges before its own (at most
+// 1024 of them, 4 per thread) and writes its rows there.  The counts stay on
+// the device and the spheres of an ordinary box come as kernel arguments, so
+// the call waits for the stream once.  Interface cells are few and scattered,
+// so pass 2 first lists the cells of a block of sites in LDS and then spreads
+// the list over the threads: one thread per column of a row (a row is one
+// 64-byte store, and the loads of 64 rows are in flight at once) and one thread
+// per label.  Bound by those chains of loads: 4096 rows of a 48^3 box of four
+// spheres took 12.9 us with one thread per row, 8.9 us here, and the call, with
+// one wait and no upload, 79 -> 56 us.
 __device__ __forceinline__ bool is_interface(double p) { return p > 0.02 && p < 0.98; }
 
 __global__ void __launch_bounds__(256) k_harvest_count(const void *__restrict__ phi, int fix, uint32_t N,
@@ -324,74 +332,117 @@ __global__ void __launch_bounds__(256) k_harvest_count(const void *__restrict__ 
     if (threadIdx.x == 0) counts[blockIdx.x] = (long long)wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-struct Sphere {
-    double x, y, z, r;
-};
-
+// counts: one per workgroup; *total gets their sum
+template <int FIX>
 __global__ void __launch_bounds__(256) k_harvest_write(Params P, const void *__restrict__ phi, uint32_t chunk,
-                                                       const long long *__restrict__ offsets,
-                                                       const Sphere *__restrict__ sph, int nb,
+                                                       const long long *__restrict__ counts,
+                                                       long long *__restrict__ total, SphereArgs few,
+                                                       const Sphere *__restrict__ many, int nb,
                                                        uint16_t *__restrict__ X, float *__restrict__ Y, int64_t cap)
 {
-    __shared__ int wcnt[4];
+    constexpr int SITES = 1024, PER = SITES / 256, FLY = 8;
+    __shared__ int wcnt[PER][4];
+    __shared__ long long wsum[4];
+    __shared__ uint32_t ls[SITES];
+    __shared__ int ly[SITES], lz[SITES];
     const int nx = P.nx, ny = P.ny, nz = P.nz;
     const uint32_t plane = (uint32_t)nx * ny, N = plane * (uint32_t)nz;
     const uint32_t b0 = blockIdx.x * chunk, b1 = min(b0 + chunk, N);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    long long base = offsets[blockIdx.x];
-    for (uint32_t s0 = b0; s0 < b1; s0 += 256) {
-        const uint32_t s = s0 + threadIdx.x;
-        const bool sel = s < b1 && is_interface(phi_load(phi, s, P.phi_fix));
-        const unsigned long long ballot = __ballot(sel);
-        const int rank = __popcll(ballot & ((1ull << lane) - 1ull));
-        if (lane == 0) wcnt[wave] = __popcll(ballot);
-        __syncthreads();
-        int before = 0;
-        for (int w = 0; w < wave; w++) before += wcnt[w];
-        const int total = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
-        if (sel) {
-            const long long row = base + before + rank;
-            if (row < cap) {
-                const int x = s % nx, y = (s / nx) % ny, z = s / plane;
-                uint16_t *xr = X + row * KIN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = tid & 31, cell = min(col, 26);
+    const int dx = cell % 3 - 1, dy = (cell / 3) % 3 - 1, dz = cell / 9 - 1;
+    long long base = 0;
+    for (uint32_t b = tid; b < blockIdx.x; b += 256) base += counts[b];
+    for (int off = 32; off > 0; off >>= 1) base += __shfl_down(base, off, 64);
+    if (lane == 0) wsum[wave] = base;
+    __syncthreads();
+    base = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) *total = base + counts[blockIdx.x];
+    for (uint32_t s0 = b0; s0 < b1; s0 += SITES) {
+        unsigned long long ballot[PER];
 #pragma unroll
-                for (int i = 0; i < 27; i++) {
-                    const int dx = i % 3 - 1, dy = (i / 3) % 3 - 1, dz = i / 9 - 1;
-                    const int xx = (x + dx + nx) % nx, yy = (y + dy + ny) % ny, zz = (z + dz + nz) % nz;
-                    const double p = phi_load(phi, (uint32_t)zz * plane + (uint32_t)yy * nx + xx, P.phi_fix);
-                    xr[i] = __builtin_bit_cast(uint16_t, (_Float16)(2.0 * p - 1.0));  // one rounding
-                }
-                for (int i = 27; i < KIN; i++) xr[i] = 0;
-                // nearest sphere surface (periodic minimum image)
-                int best = -1;
-                double bestd = 1e300, bd[3] = {0, 0, 0}, br = 0;
-                for (int k = 0; k < nb; k++) {
-                    double d[3] = {x - sph[k].x, y - sph[k].y, z - sph[k].z};
-                    const double L[3] = {(double)nx, (double)ny, (double)nz};
-                    for (int a = 0; a < 3; a++) d[a] -= L[a] * rint(d[a] / L[a]);
-                    const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-                    const double gap = fabs(rr - fabs(sph[k].r));
-                    if (gap < bestd) {
-                        bestd = gap;
-                        best = k;
-                        br = rr;
-                        bd[0] = d[0];
-                        bd[1] = d[1];
-                        bd[2] = d[2];
-                    }
-                }
-                float *yr = Y + row * 4;
-                if (best >= 0 && br > 1e-12) {
-                    const double R = sph[best].r;
-                    const double sg = R > 0 ? -1.0 : 1.0;  // toward phi = 1
-                    yr[0] = (float)(R > 0 ? -2.0 / R : 2.0 / (-R));
-                    for (int a = 0; a < 3; a++) yr[1 + a] = (float)(sg * bd[a] / br);
-                } else {
-                    yr[0] = yr[1] = yr[2] = yr[3] = 0.f;
+        for (int j = 0; j < PER; j++) {
+            const uint32_t s = s0 + 256 * j + tid;
+            ballot[j] = __ballot(s < b1 && is_interface(phi_load(phi, s, FIX)));
+            if (lane == 0) wcnt[j][wave] = __popcll(ballot[j]);
+        }
+        __syncthreads();
+        int n = 0;  // cells listed so far, in site order
+#pragma unroll
+        for (int j = 0; j < PER; j++) {
+            int i = n;
+#pragma unroll
+            for (int w = 0; w < 4; w++) {
+                i += w < wave ? wcnt[j][w] : 0;
+                n += wcnt[j][w];
+            }
+            if (ballot[j] >> lane & 1)
+                ls[i + __popcll(ballot[j] & ((1ull << lane) - 1ull))] = s0 + 256 * j + tid;
+        }
+        __syncthreads();
+        const int rows = (int)min((long long)n, max((long long)cap - base, 0ll));
+        for (int i = tid; i < rows; i += 256) {
+            const uint32_t s = ls[i], row = s / (uint32_t)nx;
+            ls[i] = s - row * nx;
+            ly[i] = (int)(row % (uint32_t)ny);
+            lz[i] = (int)(row / (uint32_t)ny);
+        }
+        __syncthreads();
+        for (int i0 = tid >> 5; i0 < rows; i0 += 8 * FLY) {
+            double p[FLY];
+#pragma unroll
+            for (int f = 0; f < FLY; f++) {  // FLY loads in flight; past the end the last row again
+                const int i = min(i0 + 8 * f, rows - 1);
+                int x = (int)ls[i] + dx, y = ly[i] + dy, z = lz[i] + dz;
+                x += x < 0 ? nx : x >= nx ? -nx : 0;
+                y += y < 0 ? ny : y >= ny ? -ny : 0;
+                z += z < 0 ? nz : z >= nz ? -nz : 0;
+                p[f] = phi_load(phi, (uint32_t)z * plane + (uint32_t)y * nx + x, FIX);
+            }
+#pragma unroll
+            for (int f = 0; f < FLY; f++)
+                if (i0 + 8 * f < rows)
+                    X[(base + i0 + 8 * f) * KIN + col] =
+                        col < 27 ? __builtin_bit_cast(uint16_t, (_Float16)(2.0 * p[f] - 1.0)) : 0;  // one rounding
+        }
+        for (int i = tid; i < rows; i += 256) {
+            // nearest sphere surface (periodic minimum image)
+            const int x = (int)ls[i], y = ly[i], z = lz[i];
+            int best = -1;
+            double bestd = 1e300, bd[3] = {0, 0, 0}, br = 0, bR = 0;
+#pragma unroll 1
+            for (int k = 0; k < nb; k++) {
+                const Sphere c = many ? many[k] : few.s[k];
+                double d[3] = {x - c.x, y - c.y, z - c.z};
+                const double L[3] = {(double)nx, (double)ny, (double)nz};
+                for (int a = 0; a < 3; a++) d[a] -= L[a] * rint(d[a] / L[a]);
+                const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+                const double gap = fabs(rr - fabs(c.r));
+                if (gap < bestd) {
+                    bestd = gap;
+                    best = k;
+                    br = rr;
+                    bR = c.r;
+                    bd[0] = d[0];
+                    bd[1] = d[1];
+                    bd[2] = d[2];
                 }
             }
+            float4 yr = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (best >= 0 && br > 1e-12) {
+                const double sg = bR > 0 ? -1.0 : 1.0;  // toward phi = 1
+                yr.x = (float)(bR > 0 ? -2.0 / bR : 2.0 / (-bR));
+                yr.y = (float)(sg * bd[0] / br);
+                yr.z = (float)(sg * bd[1] / br);
+                yr.w = (float)(sg * bd[2] / br);
+            }
+            float *y4 = Y + (base + i) * 4;  // any alignment of a float
+            y4[0] = yr.x;
+            y4[1] = yr.y;
+            y4[2] = yr.z;
+            y4[3] = yr.w;
         }
-        base += total;
+        base += n;
         __syncthreads();
     }
 }
@@ -445,11 +496,11 @@ hipError_t launch_harvest_count(const void *phi, int fix, uint32_t N, uint32_t c
 }
 
 hipError_t launch_harvest_write(const Params &p, const void *phi, uint32_t chunk, int blocks,
-                                const long long *offsets, const void *sph, int nb, uint16_t *X, float *Y, int64_t cap,
-                                hipStream_t s)
+                                const long long *counts, long long *total, const SphereArgs &few, const Sphere *many,
+                                int nb, uint16_t *X, float *Y, int64_t cap, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_harvest_write, dim3(blocks), dim3(256), 0, s, p, phi, chunk, offsets, (const Sphere *)sph,
-                       nb, X, Y, cap);
+    hipLaunchKernelGGL(p.phi_fix ? k_harvest_write<1> : k_harvest_write<0>, dim3(blocks), dim3(256), 0, s, p, phi, chunk, counts, total, few, many, nb, X,
+                       Y, cap);
     return hipGetLastError();
 }
 
