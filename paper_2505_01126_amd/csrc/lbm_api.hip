@@ -193,7 +193,6 @@ struct lbm_handle {
     int64_t steps = 0;
     bool mlp_set = false;
     lbm_batch *self = nullptr;  // lbm_step runs the box as a one-member batch
-    std::vector<float> frow_host, fx_host;
     std::string err;
 
     void *f(int k) { return ws + L.f[k]; }
@@ -293,72 +292,28 @@ int lbm_init(lbm_handle **out, const lbm_config *cfg, void *d_ws, size_t ws_byte
     set_tiling(P, lbm::TX, cfg->zchunk > 0 ? cfg->zchunk : cfg->nz);  // a batch chooses its own
 
     if (cfg->n_modes > 0) {
-        // body-force tables in FP64 on the host, stored as FP32: per mode,
-        // B = A e^{i (ky ty + kz tz)} is folded into the row coefficients of
-        // cos(|kx| t) (Re B) and sin(|kx| t) (-sign(kx) Im B), t = 2 pi x / nx
-        const int nx = cfg->nx, ny = cfg->ny, nz = cfg->nz, nm = cfg->n_modes;
-        h->frow_host.assign((size_t)lbm::FROW * ny * nz, 0.0f);
-        h->fx_host.assign((size_t)4 * nx, 0.0f);
+        // The body-force tables are formed on the device (k_forcing) from the
+        // modes and the unit circle of each axis, cos and sin of 2 pi f / n;
+        // these wait in the second population buffer, free until the first
+        // step (8^3 sites, the smallest box, leave it 27 KB; 64 modes take 4.6).
+        const int nm = cfg->n_modes, n[3] = {cfg->nx, cfg->ny, cfg->nz};
         const double two_pi = 6.283185307179586476925286766559;
-        auto twiddle = [&](long k, long v, long n, double &c, double &s) {
-            const long f = ((k * v) % n + n) % n;  // exact phase index
-            c = std::cos(two_pi * (double)f / n);
-            s = std::sin(two_pi * (double)f / n);
-        };
-        std::vector<double> ey(2 * (size_t)nm * ny), ez(2 * (size_t)nm * nz);
-        for (int m = 0; m < nm; m++) {
-            const double *r = cfg->modes + 9 * m;
-            for (int y = 0; y < ny; y++) twiddle((long)r[1], y, ny, ey[2 * ((size_t)m * ny + y)], ey[2 * ((size_t)m * ny + y) + 1]);
-            for (int z = 0; z < nz; z++) twiddle((long)r[2], z, nz, ez[2 * ((size_t)m * nz + z)], ez[2 * ((size_t)m * nz + z) + 1]);
-        }
-        double acc[lbm::FROW];
-        for (int z = 0; z < nz; z++)
-            for (int y = 0; y < ny; y++) {
-                std::fill(acc, acc + lbm::FROW, 0.0);
-                for (int m = 0; m < nm; m++) {
-                    const double *r = cfg->modes + 9 * m;
-                    const long kx = (long)r[0];
-                    const double *cy = &ey[2 * ((size_t)m * ny + y)], *cz = &ez[2 * ((size_t)m * nz + z)];
-                    const double pc = cy[0] * cz[0] - cy[1] * cz[1], ps = cy[0] * cz[1] + cy[1] * cz[0];
-                    const int kk = (int)(kx < 0 ? -kx : kx);
-                    const double sg = kx < 0 ? -1.0 : 1.0;
-                    for (int a = 0; a < 3; a++) {
-                        const double ar = r[3 + 2 * a], ai = r[4 + 2 * a];
-                        const double br = ar * pc - ai * ps, bi = ar * ps + ai * pc;
-                        if (kk == 0) {
-                            acc[a] += br;
-                        } else {
-                            acc[3 + 6 * (kk - 1) + a] += br;
-                            acc[6 + 6 * (kk - 1) + a] -= sg * bi;
-                        }
-                    }
-                }
-                float *dst = &h->frow_host[((size_t)z * ny + y) * lbm::FROW];
-                for (int k = 0; k < lbm::FROW; k++) dst[k] = (float)acc[k];
+        std::vector<double> in(cfg->modes, cfg->modes + 9 * (size_t)nm);
+        in.reserve(in.size() + 2 * ((size_t)n[0] + n[1] + n[2]));
+        for (int a = 0; a < 3; a++)
+            for (int f = 0; f < n[a]; f++) {
+                in.push_back(std::cos(two_pi * (double)f / n[a]));
+                in.push_back(std::sin(two_pi * (double)f / n[a]));
             }
-        for (int x = 0; x < nx; x++) {
-            double c, s;
-            twiddle(1, x, nx, c, s);
-            h->fx_host[4 * x + 0] = (float)c;
-            h->fx_host[4 * x + 1] = (float)s;
-            twiddle(2, x, nx, c, s);
-            h->fx_host[4 * x + 2] = (float)c;
-            h->fx_host[4 * x + 3] = (float)s;
-        }
         float *drow = (float *)(h->ws + L.frow);
         float4 *dx = (float4 *)(h->ws + L.fx);
-        hipError_t e = hipMemcpyAsync(drow, h->frow_host.data(), sizeof(float) * h->frow_host.size(),
-                                      hipMemcpyHostToDevice, h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(dx, h->fx_host.data(), sizeof(float) * h->fx_host.size(), hipMemcpyHostToDevice,
-                               h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // host staging is released below
-        h->frow_host.clear();
-        h->frow_host.shrink_to_fit();
-        h->fx_host.clear();
-        h->fx_host.shrink_to_fit();
+        double *din = (double *)h->f(1);
+        hipError_t e = hipMemcpyAsync(din, in.data(), sizeof(double) * in.size(), hipMemcpyHostToDevice, h->stream);
+        if (e == hipSuccess) e = lbm::launch_forcing(din, nm, cfg->nx, cfg->ny, cfg->nz, drow, dx, h->stream);
+        const hipError_t w = hipStreamSynchronize(h->stream);  // the host table is released below
+        if (e == hipSuccess) e = w;
         if (e != hipSuccess) {
-            g_init_err = std::string("forcing table upload: ") + hipGetErrorString(e);
+            g_init_err = std::string("forcing tables: ") + hipGetErrorString(e);
             delete h;
             return LBM_EHIP;
         }

@@ -17,8 +17,8 @@ constexpr int NRED = 10;
 constexpr int RED_BLOCKS = 768;   // fixed grid of the reduction (deterministic order): three per CU
 constexpr int QCOUNTERS = 2;  // work-queue counters of one kernel kind (one per launch parity)
 
-// Body-force tables, built on the host in FP64 from the mode table (|kx| <= 2)
-// and stored as FP32:
+// Body-force tables, formed in FP64 from the mode table (|kx| <= 2) and stored
+// as FP32:
 //   frow [nz * ny][16] per x-row (y, z): P0 (3), P1 (3), Q1 (3), P2 (3), Q2 (3), pad,
 //        the coefficients of a(x) = P0 + P1 cos t + Q1 sin t + P2 cos 2t + Q2 sin 2t
 //        with t = 2 pi x / nx (modes grouped by |kx|, the y and z phases folded in);
@@ -101,6 +101,8 @@ int ac_stage_grid(int tile);
 hipError_t launch_ac_stage_batch(const Params *tab, const Buffers *buf, const uint32_t *first, int nbox,
                                  uint32_t *counter, int parity, double rk_a, double rk_b, int tile, int grid,
                                  hipStream_t s);
+// the body-force tables: in = modes [nm][9], then (cos, sin)(2 pi f / n) for f < n along x, y and z
+hipError_t launch_forcing(const double *in, int nm, int nx, int ny, int nz, float *frow, float4 *fx, hipStream_t s);
 hipError_t launch_moments(const Params &p, int storage, const void *fin, const void *phi, float *rho, float *pr,
                           float *u, double *phi_out, hipStream_t s);
 constexpr int HARVEST_BLOCKS = 1024;
