@@ -570,12 +570,14 @@ int default_tile(const lbm_batch *b)
 // planes, 134 at 32; 32^3 single phase: 9 and 38); a large one keeps the
 // longest item that still runs at full rate: longer ones leave the
 // last round idle and spread the planes in flight over more of memory (512^3
-// FP32: 6.75 ms at 16 planes, 6.92 at 32; FP16: 4.61 at 32, 4.79 at 16; single
-// phase, which has no prologue: FP32 5.29 ms at 2, 5.51 at 8, FP16 3.00 at 4).
+// FP32: 6.75 ms at 16 planes, 6.92 at 32; with the learned curvature, whose pass
+// checks and stages every item, 7.25 at 16, 7.15 at 32; FP16: 4.61 at 32, 4.79
+// at 16; single phase, which has no prologue: FP32 5.29 ms at 2, 5.51 at 8, FP16
+// 3.00 at 4).
 int default_zchunk(const lbm_batch *b, int tile, int slots)
 {
     const bool half = b->storage != LBM_STORE_F32;
-    const int lo = b->tp ? 1 : 2, hi = b->tp ? (half ? 32 : 16) : (half ? 4 : 2);
+    const int lo = b->tp ? 1 : 2, hi = b->tp ? (half || b->ml ? 32 : 16) : (half ? 4 : 2);
     int best = lo;
     double cost = 0.0;
     for (int c = lo; c <= hi; c++) {

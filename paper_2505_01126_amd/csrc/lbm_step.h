@@ -168,9 +168,10 @@ template <class T> __device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, 
 // L2 and the Infinity Cache, so caching them only evicts input lines that
 // neighbouring work items still fetch (measured 2-4 % faster per step on
 // 512^3).  The step uses them only where every tile row covers whole 128-byte
-// lines: a partial line written past the caches measured slower (a batch of
-// boxes with edges 32-96, 8 % slower).  Loads keep the default policy:
-// non-temporal loads measured slower.
+// lines (a partial line written past the caches measured slower: a batch of
+// boxes with edges 32-96, 8 %) and the populations exceed the Infinity Cache,
+// which otherwise holds them for the next step.  Loads keep the default
+// policy: non-temporal loads measured slower.
 constexpr int STORE_NT = 2;
 template <class T, int AUX = 0>
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, T v)
