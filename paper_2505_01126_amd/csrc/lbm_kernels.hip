@@ -97,12 +97,14 @@ template <bool ROW> struct RowMarch {
             v[i] = bload<E>(r, vcol(i / 3, i % 3) * (uint32_t)sizeof(E), srow(i / 3) * (uint32_t)sizeof(E));
     }
     // base may be null: a buffer of no bytes, whose stores the hardware drops.
+    // Its scalar offset is zero then: the range check is vector offset >= bytes -
+    // scalar offset, a difference that must not go below zero.
     // Non-temporal: nothing here reads the outputs (512^3 read-out 4.13 -> 4.00 ms)
     template <class E> __device__ __forceinline__ void put(E *base, int z, E v) const
     {
         const uint32_t bytes = base ? plane * (uint32_t)sizeof(E) : 0u;
         bstore<E, STORE_NT>(plane_rsrc(base ? base + (uint32_t)z * plane : base, bytes),
-                            vcol(1, 1) * (uint32_t)sizeof(E), srow(1) * (uint32_t)sizeof(E), v);
+                            vcol(1, 1) * (uint32_t)sizeof(E), base ? srow(1) * (uint32_t)sizeof(E) : 0u, v);
     }
 };
 int64_t march_tiles(const Params &p, int wx)
