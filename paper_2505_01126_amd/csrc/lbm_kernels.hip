@@ -17,7 +17,7 @@ extern template hipError_t step_launch<2>(const Params *, const Buffers *, const
                                           bool, bool, bool, bool, int, bool, int, hipStream_t);
 
 // ------------------------------------------------------------- row marches
-// The kernels below walk a box as the step does: a workgroup takes 256 sites of
+// The marches below walk a box as the step does: a workgroup takes 256 sites of
 // a plane through a chunk of z planes, one site per lane, so that the sums over a
 // plane of a stencil are formed once and carried to the two planes above, and
 // the addresses are 32-bit offsets in one plane (a thread per site, gathering
@@ -27,8 +27,7 @@ extern template hipError_t step_launch<2>(const Params *, const Buffers *, const
 // wx > 0: each wave takes 64 sites of one x-row, so that rows are wave-uniform
 // (scalar offsets), and wx waves stand side by side in x: the lines that a
 // shifted row of populations shares with the next 64 sites are then fetched
-// once (single-phase FP16 reduction at 256^3: 197 us with four side by side, 249
-// with four rows of 64).  With the phase field and 16-bit populations the waves
+// once.  With the phase field and 16-bit populations the waves
 // take four rows instead, which then share their phi rows (512^3 FP16 read-out:
 // 2.62 ms against 2.77).  Lanes past the box's edge repeat a periodic image and
 // its writes (the same bits), so that no memory operation is conditional and the
@@ -113,14 +112,36 @@ int64_t march_tiles(const Params &p, int wx)
     const int wy = 4 / wx;
     return (int64_t)((p.nx + 64 * wx - 1) / (64 * wx)) * ((p.ny + wy - 1) / wy);
 }
-// planes per workgroup: enough workgroups to fill the chip, at most `most`
-// (the chunk's first two planes of sums are extra work; without them a longer
-// chunk gains nothing)
-int march_chunk(const Params &p, int wx, int most = 16)
+// planes per workgroup: enough workgroups to fill the chip, at most 16 (the
+// chunk's first two planes of sums are extra work)
+int march_chunk(const Params &p, int wx)
 {
     const int64_t c = march_tiles(p, wx) * p.nz / (2 * RED_BLOCKS);
-    return (int)(c < 1 ? 1 : (c < most ? c : most));
+    return (int)(c < 1 ? 1 : (c < 16 ? c : 16));
 }
+
+// How a kernel goes through a box: by sites, one thread per site, or by a march.
+struct Plan {
+    bool sites;
+    int wx, chunk;
+};
+Plan plan_init(const Params &p)
+{
+    const int wx = march_wx(p, false);
+    return {false, wx, march_chunk(p, wx)};
+}
+// Read-out (fields) and reduction.  In single phase there is no stencil whose sums
+// a march could carry, and a thread per site reads its 27 populations as fast or
+// faster: FP16 reduction of 190^3 in 96 us against 230, of 256^3 in 203 against
+// 266; FP32 read-out of 190^3 in 176 us against 195, of 257 x 255 x 256 in 393
+// against 454.
+Plan plan_read(const Params &p, int storage)
+{
+    if (!p.two_phase) return {true, 0, 0};
+    const int wx = march_wx(p, storage != 0);
+    return {false, wx, march_chunk(p, wx)};
+}
+uint32_t site_blocks(const Params &p) { return ((uint32_t)p.nx * p.ny * p.nz + NTHREADS - 1) / NTHREADS; }
 uint32_t march_items(const Params &p, int chunk, int wx)
 {
     return (uint32_t)(march_tiles(p, wx) * ((p.nz + chunk - 1) / chunk));
@@ -129,10 +150,45 @@ uint32_t march_items(const Params &p, int chunk, int wx)
 // ----------------------------------------------------------- initial state
 // f^0 = f^eq(p*0, u0) + w H : A0 / (2 c_s^4), A0 = -c_s^2 tau (grad u0 + grad u0^T),
 // written pre-shifted (slot of x - c_i) so that the first pull yields f^0 at x.
-// FP64 throughout.  Each plane of u0 is loaded once, for the gradients of the
-// three planes it enters (27 loads per site instead of 81): the sums of site
-// z+1 and z+2 are under way while those of z are completed, each in the order
-// of the velocities.
+// FP64 throughout.
+//
+// The populations h_i of a site with velocity u, its gradient G[a][b] = d_b u_a,
+// phase field ph and pressure ps: put(i, h_i)
+template <class Put>
+__device__ __forceinline__ void init_pops(const Params &P, const double (&u)[3], const double (&G)[3][3], double ph,
+                                          double ps, Put put)
+{
+    double tau = 1.0 / (double)P.omega;
+    if (P.two_phase && P.tau_g > 0.0f) {  // relaxation time of the initial phase field
+        const double c = fmin(fmax(ph, 0.0), 1.0);
+        tau = c * (double)P.tau_l + (1.0 - c) * (double)P.tau_g;
+    }
+    double A[3][3];
+#pragma unroll
+    for (int a = 0; a < 3; a++)
+        for (int b = 0; b < 3; b++) A[a][b] = -(tau / 3.0) * (G[a][b] + G[b][a]);
+    const double dp = ps - (double)P.p0;
+    const double u2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+#pragma unroll
+    for (int i = 0; i < 27; i++) {
+        const double c[3] = {(double)CX(i), (double)CY(i), (double)CZ(i)};
+        const double cu = c[0] * u[0] + c[1] * u[1] + c[2] * u[2];
+        double hA = 0.0;
+        for (int a = 0; a < 3; a++)
+            for (int b = 0; b < 3; b++) hA += (c[a] * c[b] - (a == b ? 1.0 / 3.0 : 0.0)) * A[a][b];
+        put(i, (float)(dp + 3.0 * cu + 4.5 * cu * cu - 1.5 * u2 + 4.5 * hA));
+    }
+}
+// nearest point of the fixed-point grid, clamped to its range [-2, 2)
+__device__ __forceinline__ int32_t phi_to_fix(double ph)
+{
+    return (int32_t)__builtin_rint(fmin(fmax(ph * 0x1p30, -0x1p31), 0x1p31 - 1.0));
+}
+
+// The march: each plane of u0 is loaded once, for the gradients of the three
+// planes it enters (27 loads per site instead of 81): the sums of site z+1 and
+// z+2 are under way while those of z are completed, each in the order of the
+// velocities.
 template <int S, bool ROW>
 __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *phi_out, float *u_out,
                                                    const double *phi0, const double *u0, const double *ps0, int chunk,
@@ -191,36 +247,16 @@ __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *
             }
         }
         const double ph = P.two_phase ? R.at(phi0, z, 1, 1) : 0.0;
-        double tau = 1.0 / (double)P.omega;
-        if (P.two_phase && P.tau_g > 0.0f) {  // relaxation time of the initial phase field
-            const double c = fmin(fmax(ph, 0.0), 1.0);
-            tau = c * (double)P.tau_l + (1.0 - c) * (double)P.tau_g;
-        }
-        double A[3][3];
-#pragma unroll
-        for (int a = 0; a < 3; a++)
-            for (int b = 0; b < 3; b++) A[a][b] = -(tau / 3.0) * (G[a][b] + G[b][a]);
-        const double dp = (ps0 ? R.at(ps0, z, 1, 1) : (double)P.p0) - (double)P.p0;
-        const double u2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
         __amdgpu_buffer_rsrc_t dst[3];  // slots of z - cz: row y - cy, column x - cx of population i
 #pragma unroll
         for (int k = 0; k < 3; k++)
             dst[k] = plane_rsrc(fout + (size_t)((uint32_t)wrapi(z + 1 - k, R.nz) * plane) * 27, 27u * plane * ES);
-#pragma unroll
-        for (int i = 0; i < 27; i++) {
-            const double c[3] = {(double)CX(i), (double)CY(i), (double)CZ(i)};
-            const double cu = c[0] * u[0] + c[1] * u[1] + c[2] * u[2];
-            double hA = 0.0;
-            for (int a = 0; a < 3; a++)
-                for (int b = 0; b < 3; b++) hA += (c[a] * c[b] - (a == b ? 1.0 / 3.0 : 0.0)) * A[a][b];
-            const double h = dp + 3.0 * cu + 4.5 * cu * cu - 1.5 * u2 + 4.5 * hA;
+        init_pops(P, u, G, ph, ps0 ? R.at(ps0, z, 1, 1) : (double)P.p0, [&](int i, float h) {
             bstore<T>(dst[CZ(i) + 1], R.vcol(1 - CY(i), 1 - CX(i)) * ES, ((uint32_t)i * plane + R.srow(1 - CY(i))) * ES,
-                      Pop<S>::enc((float)h));
-        }
-        if (P.phi_fix)  // nearest point of the fixed-point grid, clamped to its range [-2, 2)
-            R.put((int32_t *)phi_out, z, (int32_t)__builtin_rint(fmin(fmax(ph * 0x1p30, -0x1p31), 0x1p31 - 1.0)));
-        else
-            R.put((double *)phi_out, z, ph);
+                      Pop<S>::enc(h));
+        });
+        if (P.phi_fix) R.put((int32_t *)phi_out, z, phi_to_fix(ph));
+        else R.put((double *)phi_out, z, ph);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
             R.put(u_out ? u_out + a * N : u_out, z, (float)u[a]);
@@ -234,13 +270,95 @@ __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *
 }
 
 // -------------------------------------------------- fields and reductions
-// Macroscopic state at time n of the sites of item L (pull + stencils from
-// global memory): use(z, state, phi, R) for each site of the box.  In the marches
+// By sites: macroscopic state at time n of site s (pull + stencils from global
+// memory).  Every lane of the wave calls this together (the network stage is a
+// wave-wide MFMA); lanes with valid == false only take part in that stage.
+template <int S, bool TP, bool FRC, bool ML>
+__device__ __forceinline__ void site_state(const Params &P, const void *fin_, const void *phi, uint32_t s, bool valid,
+                                           Macro &m, const MlpW &W, MlpWave &wv)
+{
+    using T = typename Pop<S>::T;
+    const T *fin = (const T *)fin_;
+    const int nx = P.nx, ny = P.ny, nz = P.nz;
+    const uint32_t plane = (uint32_t)nx * ny;
+    const int x = s % nx, y = (s / nx) % ny, z = s / plane;
+    // the periodic neighbours' coordinates, once per site: index k = 1 + offset
+    const uint32_t xk[3] = {(uint32_t)wrapi(x - 1, nx), (uint32_t)x, (uint32_t)wrapi(x + 1, nx)};
+    const uint32_t yk[3] = {(uint32_t)wrapi(y - 1, ny) * nx, (uint32_t)y * nx, (uint32_t)wrapi(y + 1, ny) * nx};
+    const uint32_t zk[3] = {(uint32_t)wrapi(z - 1, nz), (uint32_t)z, (uint32_t)wrapi(z + 1, nz)};
+    M10 M;
+    PhiGrad G;
+    float ph[27];
+    float kfd = 0.f, gn = 0.f, cs = 0.f;
+    bool sel = false;
+    if (valid) {
+        float hv[27];
+#pragma unroll
+        for (int i = 0; i < 27; i++)  // population i of site s - c_i
+            hv[i] = Pop<S>::dec(fin[((size_t)zk[1 - CZ(i)] * 27 + i) * plane + yk[1 - CY(i)] + xk[1 - CX(i)]]);
+        moments10(hv, M);
+        if constexpr (TP) {
+            M10 Mp;
+#pragma unroll
+            for (int i = 0; i < 27; i++)
+                ph[i] = (float)phi_load(phi, zk[1 + CZ(i)] * plane + yk[1 + CY(i)] + xk[1 + CX(i)], P.phi_fix);
+            phi_stencil(ph, Mp, G);
+            cs = surface_coef<ML>(Mp, G, P);
+            if constexpr (ML) sel = mlp_select(G, P, kfd, gn);
+        }
+    }
+    float fs[3] = {0.f, 0.f, 0.f};
+    if constexpr (TP) {
+        if (valid)
+#pragma unroll
+            for (int a = 0; a < 3; a++) fs[a] = cs * G.g[a];
+    }
+    if constexpr (ML) {
+        float yv[4] = {0.f, 0.f, 0.f, 0.f};
+        mlp_wave(W, wv, sel, ph, yv, threadIdx.x & 63);
+        if (sel) surface_blend(G, cs, P, kfd, gn, yv, fs);
+    }
+    if (valid) {
+        float aext[3] = {0.f, 0.f, 0.f};
+        if constexpr (FRC) forcing_at<false>(P, P.fx[x], (uint32_t)z * ny + y, aext);
+        site_macro<TP>(M, G, fs, aext, P, m);
+    }
+}
+
+template <int S, bool TP, bool FRC, bool ML>
+__global__ void __launch_bounds__(NTHREADS) k_moments_site(Params P, const void *fin, const void *phi, float *rho,
+                                                           float *pr, float *u, double *phi_out)
+{
+    __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
+    MlpW &W = *(MlpW *)mlp_raw;
+    MlpWave *wv = (MlpWave *)(mlp_raw + (ML ? sizeof(MlpW) : 0));
+    if constexpr (ML) {
+        load_weights((const uint16_t *)P.mlp, W, threadIdx.x);
+        __syncthreads();
+    }
+    const uint32_t N = (uint32_t)P.nx * P.ny * P.nz;
+    const uint32_t s = blockIdx.x * NTHREADS + threadIdx.x;
+    const bool valid = s < N;
+    Macro m;
+    site_state<S, TP, FRC, ML>(P, fin, phi, valid ? s : 0u, valid, m, W, wv[ML ? threadIdx.x >> 6 : 0]);
+    if (!valid) return;
+    if (rho) rho[s] = m.rho;
+    if (pr) pr[s] = (P.p0 + m.dp) * m.rho * (1.0f / 3.0f);
+    if (u) {
+        u[s] = m.u[0];
+        u[(size_t)N + s] = m.u[1];
+        u[2 * (size_t)N + s] = m.u[2];
+    }
+    if (phi_out) phi_out[s] = TP ? phi_load(phi, s, P.phi_fix) : 0.0;
+}
+
+// The march: macroscopic state at time n of the sites of item L (pull + stencils
+// from global memory): use(z, state, phi, R) for each site of the box.  In the marches
 // by rows (the long ones) and without the network, the populations and the phi
 // plane of the next site are in flight while this one is worked on.  Bound by
 // memory: 512^3 read-out, FP16 4.03 -> 2.6 ms, FP32 4.46 -> 4.0 ms (4.8 TB/s);
 // reduction, FP32 4.53 -> 3.33 ms (4.7 TB/s).
-template <int S, bool TP, bool FRC, bool ML, bool FX, bool ROW, class Use>
+template <int S, bool FRC, bool ML, bool FX, bool ROW, class Use>
 __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, const void *phi_, uint32_t L, int chunk,
                                           int wx, const MlpW &W, MlpWave &wv, Use use)
 {
@@ -273,7 +391,7 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
     float ph[27];  // ... or, for the network's inputs, the three planes themselves
     PT c = 0, r[9];
     float v[9];
-    if constexpr (TP) {
+    {
         PT ra[9], rb[9];
         R.at9(phi, R.z0 - 1, ra);
         R.at9(phi, R.z0, rb);
@@ -289,7 +407,7 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
     }
     auto fetch = [&](int z) {
         fetch_pops(z);
-        if constexpr (TP) R.at9(phi, z + 1, r);
+        R.at9(phi, z + 1, r);
     };
     constexpr bool AHEAD = ROW && !ML;
     auto site = [&](int z, int zn) {
@@ -304,7 +422,7 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
             for (int i = 0; i < 27; i++) hf[i] = Pop<S>::dec(hv[i]);
             moments10(hf, M);
         }
-        if constexpr (TP) {
+        {
             M10 Mp;
             f32(r, v);
             c_next = r[4];
@@ -324,22 +442,20 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
             if constexpr (ML) sel = mlp_select(G, P, kfd, gn);  // images too: they write what the owner writes
         }
         if constexpr (AHEAD) fetch(zn);
-        float fs[3] = {0.f, 0.f, 0.f};
-        if constexpr (TP) {
+        float fs[3];
 #pragma unroll
-            for (int a = 0; a < 3; a++) fs[a] = cs * G.g[a];
-            if constexpr (ML) {
-                if (__ballot(sel)) {  // the network: a wave-wide MFMA, so every lane takes part
-                    float y[4] = {0.f, 0.f, 0.f, 0.f};
-                    mlp_wave(W, wv, sel, ph, y, threadIdx.x & 63);
-                    if (sel) surface_blend(G, cs, P, kfd, gn, y, fs);
-                }
+        for (int a = 0; a < 3; a++) fs[a] = cs * G.g[a];
+        if constexpr (ML) {
+            if (__ballot(sel)) {  // the network: a wave-wide MFMA, so every lane takes part
+                float y[4] = {0.f, 0.f, 0.f, 0.f};
+                mlp_wave(W, wv, sel, ph, y, threadIdx.x & 63);
+                if (sel) surface_blend(G, cs, P, kfd, gn, y, fs);
             }
         }
         float aext[3] = {0.f, 0.f, 0.f};
         if constexpr (FRC) forcing_at<ROW>(P, ex, (uint32_t)z * R.ny + R.y, aext);
         Macro m;
-        site_macro<TP>(M, G, fs, aext, P, m);
+        site_macro<true>(M, G, fs, aext, P, m);
         use(z, m, FX ? (double)c * 0x1p-30 : (double)c, R);
         c = c_next;
     };
@@ -355,7 +471,7 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
     }
 }
 
-template <int S, bool TP, bool FRC, bool ML, bool FX, bool ROW>
+template <int S, bool FRC, bool ML, bool FX, bool ROW>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ML || !ROW ? 3 : 4)))
 k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, float *u, double *phi_out, int chunk, int wx)
 {
@@ -367,13 +483,13 @@ k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, flo
         __syncthreads();
     }
     const size_t N = (size_t)P.nx * P.ny * P.nz;
-    read_tile<S, TP, FRC, ML, FX, ROW>(P, fin, phi, blockIdx.x, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
-                                       [&](int z, const Macro &m, double ph, const RowMarch<ROW> &R) {
+    read_tile<S, FRC, ML, FX, ROW>(P, fin, phi, blockIdx.x, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
+                                   [&](int z, const Macro &m, double ph, const RowMarch<ROW> &R) {
         R.put(rho, z, m.rho);
         R.put(pr, z, (P.p0 + m.dp) * m.rho * (1.0f / 3.0f));
 #pragma unroll
         for (int a = 0; a < 3; a++) R.put(u ? u + a * N : u, z, m.u[a]);
-        R.put(phi_out, z, TP ? ph : 0.0);
+        R.put(phi_out, z, ph);
     });
 }
 
@@ -429,12 +545,72 @@ __device__ __forceinline__ void block_reduce(const double (&acc)[NRED], double (
     }
 }
 
-// FP64 partial sums per block over a fixed partition of the items, combined in
-// a fixed order: the result does not depend on scheduling.  With the
+// The ten statistics of one site added to a thread's; phi_sum: phi, or with the
+// fixed-point phi the integer q
+template <bool TP>
+__device__ __forceinline__ void accumulate(const Params &P, const Macro &m, double ph, double phi_sum,
+                                           double (&acc)[NRED])
+{
+    const double r = m.rho, pstar = (double)P.p0 + (double)m.dp;
+    const double ux = m.u[0], uy = m.u[1], uz = m.u[2];
+    const bool bad = !isfinite(pstar) || !isfinite(ux) || !isfinite(uy) || !isfinite(uz) || !isfinite(ph);
+    if (bad) {
+        acc[9] += 1.0;
+        return;
+    }
+    const double u2 = ux * ux + uy * uy + uz * uz;
+    acc[0] += phi_sum;
+    acc[1] += r;
+    acc[2] += pstar;
+    acc[3] += r * ux;
+    acc[4] += r * uy;
+    acc[5] += r * uz;
+    acc[6] += 0.5 * r * u2;
+    acc[7] = fmax(acc[7], u2);  // the root of the largest at the end
+    acc[8] = TP ? fmax(acc[8], fmax(ph - 1.0, fmax(-ph, 0.0))) : 0.0;
+}
+__device__ __forceinline__ void put_partials(double (&acc)[NRED], double *partials)
+{
+    acc[7] = sqrt(acc[7]);
+    __shared__ double wred[NTHREADS / 64][NRED];
+    double res = 0.0;
+    block_reduce(acc, wred, res);
+    if (threadIdx.x < NRED) partials[(size_t)blockIdx.x * NRED + threadIdx.x] = res;
+}
+
+// FP64 partial sums per block over a fixed partition of the sites or items,
+// combined in a fixed order: the result does not depend on scheduling.  With the
 // fixed-point phi, sum phi is accumulated as the integer sum of q (exact in
 // the FP64 block partials, which stay below 2^53, and in the final int64 sum),
 // so it is a function of that integer alone.
-template <int S, bool TP, bool FRC, bool ML, bool FX, bool ROW>
+template <int S, bool TP, bool FRC, bool ML>
+__global__ void __launch_bounds__(NTHREADS) k_reduce_site(Params P, const void *fin, const void *phi, double *partials)
+{
+    __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
+    MlpW &W = *(MlpW *)mlp_raw;
+    MlpWave *wv = (MlpWave *)(mlp_raw + (ML ? sizeof(MlpW) : 0));
+    if constexpr (ML) {
+        load_weights((const uint16_t *)P.mlp, W, threadIdx.x);
+        __syncthreads();
+    }
+    const uint32_t N = (uint32_t)P.nx * P.ny * P.nz;
+    double acc[NRED];
+#pragma unroll
+    for (int k = 0; k < NRED; k++) acc[k] = 0.0;
+    // uniform trip count across the block (the network stage is wave-wide)
+    for (uint32_t base = blockIdx.x * NTHREADS; base < N; base += gridDim.x * NTHREADS) {
+        const uint32_t s = base + threadIdx.x;
+        const bool valid = s < N;
+        Macro m;
+        site_state<S, TP, FRC, ML>(P, fin, phi, valid ? s : 0u, valid, m, W, wv[ML ? threadIdx.x >> 6 : 0]);
+        if (!valid) continue;
+        const double ph = TP ? phi_load(phi, s, P.phi_fix) : 0.0;
+        accumulate<TP>(P, m, ph, P.phi_fix ? ph * 0x1p30 : ph, acc);
+    }
+    put_partials(acc, partials);
+}
+
+template <int S, bool FRC, bool ML, bool FX, bool ROW>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3)))
 k_reduce(Params P, const void *fin, const void *phi, double *partials, uint32_t items, int chunk, int wx)
 {
@@ -449,33 +625,11 @@ k_reduce(Params P, const void *fin, const void *phi, double *partials, uint32_t 
 #pragma unroll
     for (int k = 0; k < NRED; k++) acc[k] = 0.0;
     for (uint32_t L = blockIdx.x; L < items; L += gridDim.x)
-        read_tile<S, TP, FRC, ML, FX, ROW>(P, fin, phi, L, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
-                                           [&](int, const Macro &m, double phv, const RowMarch<ROW> &R) {
-            if (!R.in_box) return;
-            const double ph = TP ? phv : 0.0;
-            const double r = m.rho, pstar = (double)P.p0 + (double)m.dp;
-            const double ux = m.u[0], uy = m.u[1], uz = m.u[2];
-            const bool bad = !isfinite(pstar) || !isfinite(ux) || !isfinite(uy) || !isfinite(uz) || !isfinite(ph);
-            if (bad) {
-                acc[9] += 1.0;
-                return;
-            }
-            const double u2 = ux * ux + uy * uy + uz * uz;
-            acc[0] += FX ? ph * 0x1p30 : ph;
-            acc[1] += r;
-            acc[2] += pstar;
-            acc[3] += r * ux;
-            acc[4] += r * uy;
-            acc[5] += r * uz;
-            acc[6] += 0.5 * r * u2;
-            acc[7] = fmax(acc[7], u2);  // the root of the largest below
-            acc[8] = TP ? fmax(acc[8], fmax(ph - 1.0, fmax(-ph, 0.0))) : 0.0;
+        read_tile<S, FRC, ML, FX, ROW>(P, fin, phi, L, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
+                                       [&](int, const Macro &m, double ph, const RowMarch<ROW> &R) {
+            if (R.in_box) accumulate<true>(P, m, ph, FX ? ph * 0x1p30 : ph, acc);
         });
-    acc[7] = sqrt(acc[7]);
-    __shared__ double wred[NTHREADS / 64][NRED];
-    double res = 0.0;
-    block_reduce(acc, wred, res);
-    if (threadIdx.x < NRED) partials[(size_t)blockIdx.x * NRED + threadIdx.x] = res;
+    put_partials(acc, partials);
 }
 
 // one wave per statistic over the RED_BLOCKS partials
@@ -580,8 +734,10 @@ hipError_t launch_ac_stage_batch(const Params *tab, const Buffers *buf, const ui
 hipError_t launch_init(const Params &p, int storage, void *fout, void *phi_out, float *u_out, const double *phi0,
                        const double *u0, const double *ps0, hipStream_t s)
 {
-    const int wx = march_wx(p, false), c = march_chunk(p, wx);
-    dim3 grid(march_items(p, c, wx)), block(NTHREADS);
+    const dim3 block(NTHREADS);
+    const Plan plan = plan_init(p);
+    const int wx = plan.wx, c = plan.chunk;
+    const dim3 grid(march_items(p, c, wx));
 #define INIT(S_, R_) \
     hipLaunchKernelGGL((k_init<S_, R_>), grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0, c, wx)
     if (wx) {
@@ -597,16 +753,18 @@ hipError_t launch_init(const Params &p, int storage, void *fout, void *phi_out, 
     return hipGetLastError();
 }
 
-// the read-out kernels also take the phi storage and the kind of march
-#define LBM_READ_CALL(S_, TP_, F_, M_)                                  \
-    {                                                                   \
-        if (TP_ && p.phi_fix) {                                         \
-            if (wx) READ(S_, TP_, F_, M_, TP_, true);                   \
-            else READ(S_, TP_, F_, M_, TP_, false);                     \
-        } else {                                                        \
-            if (wx) READ(S_, TP_, F_, M_, false, true);                 \
-            else READ(S_, TP_, F_, M_, false, false);                   \
-        }                                                               \
+// the marches of the read-out also take the phi storage and the kind of march
+#define LBM_MARCH_CALL(S_, TP_, F_, M_)                 \
+    {                                                   \
+        if constexpr (TP_) {                            \
+            if (p.phi_fix) {                            \
+                if (wx) MARCH(S_, F_, M_, true, true);  \
+                else MARCH(S_, F_, M_, true, false);    \
+            } else {                                    \
+                if (wx) MARCH(S_, F_, M_, false, true); \
+                else MARCH(S_, F_, M_, false, false);   \
+            }                                           \
+        }                                               \
     }
 
 // ------------------------------------------------------------ body force
@@ -681,27 +839,45 @@ hipError_t launch_forcing(const double *in, int nm, int nx, int ny, int nz, floa
 hipError_t launch_moments(const Params &p, int storage, const void *fin, const void *phi, float *rho, float *pr,
                           float *u, double *phi_out, hipStream_t s)
 {
-    const int wx = march_wx(p, p.two_phase && storage != 0), c = march_chunk(p, wx, p.two_phase ? 16 : 4);
-    dim3 grid(march_items(p, c, wx)), block(NTHREADS);
     const bool tp = p.two_phase != 0, frc = p.n_modes > 0, ml = p.curv_mode == 1;
-#define READ(S_, TP_, F_, M_, X_, R_) \
-    hipLaunchKernelGGL((k_moments<S_, TP_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out, c, wx)
-    LBM_DISPATCH(storage, tp, frc, ml, LBM_READ_CALL);
-#undef READ
+    const dim3 block(NTHREADS);
+    const Plan plan = plan_read(p, storage);
+    if (plan.sites) {
+        const dim3 grid(site_blocks(p));
+#define SITE(S_, TP_, F_, M_) \
+    hipLaunchKernelGGL((k_moments_site<S_, TP_, F_, M_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out);
+        LBM_DISPATCH(storage, tp, frc, ml, SITE);
+#undef SITE
+        return hipGetLastError();
+    }
+    const int wx = plan.wx, c = plan.chunk;
+    const dim3 grid(march_items(p, c, wx));
+#define MARCH(S_, F_, M_, X_, R_) \
+    hipLaunchKernelGGL((k_moments<S_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out, c, wx)
+    LBM_DISPATCH(storage, tp, frc, ml, LBM_MARCH_CALL);
+#undef MARCH
     return hipGetLastError();
 }
 
 hipError_t launch_reduce(const Params &p, int storage, const void *fin, const void *phi, double *partials,
                          double *out, hipStream_t s)
 {
-    const int wx = march_wx(p, p.two_phase && storage != 0), c = march_chunk(p, wx);
-    const uint32_t items = march_items(p, c, wx);
-    dim3 grid(RED_BLOCKS), block(NTHREADS);
     const bool tp = p.two_phase != 0, frc = p.n_modes > 0, ml = p.curv_mode == 1;
-#define READ(S_, TP_, F_, M_, X_, R_) \
-    hipLaunchKernelGGL((k_reduce<S_, TP_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, partials, items, c, wx)
-    LBM_DISPATCH(storage, tp, frc, ml, LBM_READ_CALL);
-#undef READ
+    const Plan plan = plan_read(p, storage);
+    const dim3 block(NTHREADS), grid(RED_BLOCKS);
+    if (plan.sites) {
+#define SITE(S_, TP_, F_, M_) \
+    hipLaunchKernelGGL((k_reduce_site<S_, TP_, F_, M_>), grid, block, 0, s, p, fin, phi, partials);
+        LBM_DISPATCH(storage, tp, frc, ml, SITE);
+#undef SITE
+    } else {
+        const int wx = plan.wx, c = plan.chunk;
+        const uint32_t items = march_items(p, c, wx);
+#define MARCH(S_, F_, M_, X_, R_) \
+    hipLaunchKernelGGL((k_reduce<S_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, partials, items, c, wx)
+        LBM_DISPATCH(storage, tp, frc, ml, LBM_MARCH_CALL);
+#undef MARCH
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64 * NRED), 0, s, partials, p.phi_fix, out);
