@@ -125,21 +125,32 @@ struct Plan {
     bool sites;
     int wx, chunk;
 };
+// The plane's sites fill less than `tenths` tenths of the lanes that a march puts
+// on it: 256 lanes walk z for 64 sites of 8 x 8, 512 for 289 of 17 x 17.
+bool thin(const Params &p, int tenths)
+{
+    return (int64_t)p.nx * p.ny * 10 < march_tiles(p, 0) * NTHREADS * tenths;
+}
+// Set-up.  By sites on thin planes (8 x 8 x 65536: 321 us against 570; 17 x 17 x
+// 4000: 127 and 140); 20 x 20, which fills 0.78 of the lanes, is even, and full
+// planes gain by the march (256^3: 0.80 against 1.1 ms).
 Plan plan_init(const Params &p)
 {
     const int wx = march_wx(p, false);
-    return {false, wx, march_chunk(p, wx)};
+    return {thin(p, 6), wx, march_chunk(p, wx)};
 }
 // Read-out (fields) and reduction.  In single phase there is no stencil whose sums
 // a march could carry, and a thread per site reads its 27 populations as fast or
 // faster: FP16 reduction of 190^3 in 96 us against 230, of 256^3 in 203 against
 // 266; FP32 read-out of 190^3 in 176 us against 195, of 257 x 255 x 256 in 393
-// against 454.
+// against 454. With the phase field the march wins except on thin planes (8 x 8 x
+// 65536: FP32 read-out 151 us by sites against 255; 17 x 17 x 4000: 35 and 42, but
+// with the fixed-point phi 46 and 34).
 Plan plan_read(const Params &p, int storage)
 {
     if (!p.two_phase) return {true, 0, 0};
     const int wx = march_wx(p, storage != 0);
-    return {false, wx, march_chunk(p, wx)};
+    return {thin(p, p.phi_fix ? 5 : 6), wx, march_chunk(p, wx)};
 }
 uint32_t site_blocks(const Params &p) { return ((uint32_t)p.nx * p.ny * p.nz + NTHREADS - 1) / NTHREADS; }
 uint32_t march_items(const Params &p, int chunk, int wx)
@@ -183,6 +194,47 @@ __device__ __forceinline__ void init_pops(const Params &P, const double (&u)[3],
 __device__ __forceinline__ int32_t phi_to_fix(double ph)
 {
     return (int32_t)__builtin_rint(fmin(fmax(ph * 0x1p30, -0x1p31), 0x1p31 - 1.0));
+}
+
+// by sites
+template <int S>
+__global__ void __launch_bounds__(NTHREADS) k_init_site(Params P, void *fout_, void *phi_out, float *u_out,
+                                                        const double *phi0, const double *u0, const double *ps0)
+{
+    using T = typename Pop<S>::T;
+    T *fout = (T *)fout_;
+    const int nx = P.nx, ny = P.ny, nz = P.nz;
+    const uint32_t plane = (uint32_t)nx * ny, N = plane * (uint32_t)nz;
+    const uint32_t s = blockIdx.x * NTHREADS + threadIdx.x;
+    if (s >= N) return;
+    const int x = s % nx, y = (s / nx) % ny, z = s / plane;
+    double u[3] = {0, 0, 0}, G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+    if (u0) {
+        for (int a = 0; a < 3; a++) u[a] = u0[(size_t)a * N + s];
+#pragma unroll
+        for (int i = 0; i < 27; i++) {
+            const uint32_t t = (uint32_t)wrapi(z + CZ(i), nz) * plane + (uint32_t)wrapi(y + CY(i), ny) * nx +
+                               (uint32_t)wrapi(x + CX(i), nx);
+            for (int a = 0; a < 3; a++) {
+                const double v = 3.0 * WTD(i) * u0[(size_t)a * N + t];
+                G[a][0] += v * CX(i);
+                G[a][1] += v * CY(i);
+                G[a][2] += v * CZ(i);
+            }
+        }
+    }
+    const double ph = P.two_phase ? phi0[s] : 0.0;
+    init_pops(P, u, G, ph, ps0 ? ps0[s] : (double)P.p0, [&](int i, float h) {
+        const size_t slot = ((size_t)wrapi(z - CZ(i), nz) * 27 + i) * plane + (uint32_t)wrapi(y - CY(i), ny) * nx +
+                            (uint32_t)wrapi(x - CX(i), nx);
+        fout[slot] = Pop<S>::enc(h);
+    });
+    if (phi_out) {
+        if (P.phi_fix) ((int32_t *)phi_out)[s] = phi_to_fix(ph);
+        else ((double *)phi_out)[s] = ph;
+    }
+    if (u_out)
+        for (int a = 0; a < 3; a++) u_out[(size_t)a * N + s] = (float)u[a];
 }
 
 // The march: each plane of u0 is loaded once, for the gradients of the three
@@ -736,6 +788,15 @@ hipError_t launch_init(const Params &p, int storage, void *fout, void *phi_out, 
 {
     const dim3 block(NTHREADS);
     const Plan plan = plan_init(p);
+    if (plan.sites) {
+        const dim3 grid(site_blocks(p));
+#define INIT(S_) hipLaunchKernelGGL(k_init_site<S_>, grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0)
+        if (storage == 0) INIT(0);
+        else if (storage == 1) INIT(1);
+        else INIT(2);
+#undef INIT
+        return hipGetLastError();
+    }
     const int wx = plan.wx, c = plan.chunk;
     const dim3 grid(march_items(p, c, wx));
 #define INIT(S_, R_) \
