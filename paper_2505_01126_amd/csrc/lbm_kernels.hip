@@ -112,11 +112,11 @@ int64_t march_tiles(const Params &p, int wx)
     const int wy = 4 / wx;
     return (int64_t)((p.nx + 64 * wx - 1) / (64 * wx)) * ((p.ny + wy - 1) / wy);
 }
-// planes per workgroup: enough workgroups to fill the chip, at most 16 (the
-// chunk's first two planes of sums are extra work)
-int march_chunk(const Params &p, int wx)
+// planes per workgroup: `rounds` workgroups for each that is resident, at most 16
+// (the chunk's first two planes of sums are extra work)
+int march_chunk(const Params &p, int wx, int rounds = 2)
 {
-    const int64_t c = march_tiles(p, wx) * p.nz / (2 * RED_BLOCKS);
+    const int64_t c = march_tiles(p, wx) * p.nz / (rounds * RED_BLOCKS);
     return (int)(c < 1 ? 1 : (c < 16 ? c : 16));
 }
 
@@ -145,11 +145,21 @@ Plan plan_init(const Params &p)
 // 266; FP32 read-out of 190^3 in 176 us against 195, of 257 x 255 x 256 in 393
 // against 454. With the phase field the march wins except on thin planes (8 x 8 x
 // 65536: FP32 read-out 151 us by sites against 255; 17 x 17 x 4000: 35 and 42, but
-// with the fixed-point phi 46 and 34).
-Plan plan_read(const Params &p, int storage)
+// with the fixed-point phi 46 and 34). With the learned curvature a wave with many
+// selected cells runs the network for them plane after plane: the march needs six
+// workgroups for each resident one to hide that, and planes that fill the lanes
+// (40 x 17 x 2000 FP16 read-out: 68 us by sites, 93 in chunks of 3; reduction of
+// 13 x 200 x 500: 72 us in chunks of 1, 111 of 3).  A read-out of less than two
+// planes per workgroup goes by sites (64^3: 22 us against 25); the reduction gains
+// from the first plane on (64^3: 29 and 35).
+Plan plan_read(const Params &p, int storage, bool fields)
 {
     if (!p.two_phase) return {true, 0, 0};
     const int wx = march_wx(p, storage != 0);
+    if (p.curv_mode == 1) {
+        const int c = march_chunk(p, wx, 6);
+        return {thin(p, 8) || (fields && c < 2), wx, c};
+    }
     return {thin(p, p.phi_fix ? 5 : 6), wx, march_chunk(p, wx)};
 }
 uint32_t site_blocks(const Params &p) { return ((uint32_t)p.nx * p.ny * p.nz + NTHREADS - 1) / NTHREADS; }
@@ -902,7 +912,7 @@ hipError_t launch_moments(const Params &p, int storage, const void *fin, const v
 {
     const bool tp = p.two_phase != 0, frc = p.n_modes > 0, ml = p.curv_mode == 1;
     const dim3 block(NTHREADS);
-    const Plan plan = plan_read(p, storage);
+    const Plan plan = plan_read(p, storage, true);
     if (plan.sites) {
         const dim3 grid(site_blocks(p));
 #define SITE(S_, TP_, F_, M_) \
@@ -924,7 +934,7 @@ hipError_t launch_reduce(const Params &p, int storage, const void *fin, const vo
                          double *out, hipStream_t s)
 {
     const bool tp = p.two_phase != 0, frc = p.n_modes > 0, ml = p.curv_mode == 1;
-    const Plan plan = plan_read(p, storage);
+    const Plan plan = plan_read(p, storage, false);
     const dim3 block(NTHREADS), grid(RED_BLOCKS);
     if (plan.sites) {
 #define SITE(S_, TP_, F_, M_) \
