@@ -32,13 +32,15 @@ extern template hipError_t step_launch<2>(const Params *, const Buffers *, const
 // 2.62 ms against 2.77).  Lanes past the box's edge repeat a periodic image and
 // its writes (the same bits), so that no memory operation is conditional and the
 // compiler counts those in flight exactly.
-// wx = 0: 256 consecutive sites of the plane, where rows of 64 would leave more
-// than a tenth of the lanes idle (72^3 FP32 read-out: 13 us against 24), and in
-// boxes too small for chunks of three planes on every compute unit.
+// wx = 0: 256 consecutive sites of the plane, in boxes too small for chunks of
+// three planes on every compute unit and where nx is no multiple of 64: rows then
+// end inside a wave and inside a memory line (190^3: reduction of FP16 133 us
+// against 145 by rows, read-out of FP32 197 us against 231; 300^3: 496 and 534,
+// 752 and 849).
 inline int march_wx(const Params &p, bool rows)
 {
     auto fits = [&](int w) { return (p.nx + w - 1) / w * w * 10 <= p.nx * 11; };
-    if (!fits(64) || (int64_t)p.nx * p.ny * p.nz < (int64_t)NTHREADS * 6 * RED_BLOCKS) return 0;
+    if (p.nx % 64 != 0 || (int64_t)p.nx * p.ny * p.nz < (int64_t)NTHREADS * 6 * RED_BLOCKS) return 0;
     return rows || !fits(128) ? 1 : (fits(256) ? 4 : 2);
 }
 template <bool ROW> struct RowMarch {
