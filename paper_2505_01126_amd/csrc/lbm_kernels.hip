@@ -100,12 +100,16 @@ template <bool ROW> struct RowMarch {
     // base may be null: a buffer of no bytes, whose stores the hardware drops.
     // Its scalar offset is zero then: the range check is vector offset >= bytes -
     // scalar offset, a difference that must not go below zero.
-    // Non-temporal: nothing here reads the outputs (512^3 read-out 4.13 -> 4.00 ms)
-    template <class E> __device__ __forceinline__ void put(E *base, int z, E v) const
+    // NT: non-temporal.  The fields of a read-out by rows go that way (512^3: 4.00
+    // ms against 4.13; read again at once, 256^3: 602 us either way).  Where rows
+    // end inside a line, and for the initial phi and u, which the first step reads,
+    // they go through the caches (150 x 141 x 203, FP32 read-out and a pass over u
+    // and phi: 161 us, 172 non-temporal; set-up of 129 x 130 x 131: 160 and 172 us).
+    template <bool NT, class E> __device__ __forceinline__ void put(E *base, int z, E v) const
     {
         const uint32_t bytes = base ? plane * (uint32_t)sizeof(E) : 0u;
-        bstore<E, STORE_NT>(plane_rsrc(base ? base + (uint32_t)z * plane : base, bytes),
-                            vcol(1, 1) * (uint32_t)sizeof(E), base ? srow(1) * (uint32_t)sizeof(E) : 0u, v);
+        bstore<E, NT ? STORE_NT : 0>(plane_rsrc(base ? base + (uint32_t)z * plane : base, bytes),
+                                     vcol(1, 1) * (uint32_t)sizeof(E), base ? srow(1) * (uint32_t)sizeof(E) : 0u, v);
     }
 };
 int64_t march_tiles(const Params &p, int wx)
@@ -339,11 +343,11 @@ __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *
             bstore<T>(dst[CZ(i) + 1], R.vcol(1 - CY(i), 1 - CX(i)) * ES, ((uint32_t)i * plane + R.srow(1 - CY(i))) * ES,
                       Pop<S>::enc(h));
         });
-        if (P.phi_fix) R.put((int32_t *)phi_out, z, phi_to_fix(ph));
-        else R.put((double *)phi_out, z, ph);
+        if (P.phi_fix) R.template put<false>((int32_t *)phi_out, z, phi_to_fix(ph));
+        else R.template put<false>((double *)phi_out, z, ph);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-            R.put(u_out ? u_out + a * N : u_out, z, (float)u[a]);
+            R.template put<false>(u_out ? u_out + a * N : u_out, z, (float)u[a]);
             u[a] = un[a];
             for (int b = 0; b < 3; b++) {
                 G[a][b] = Gn[a][b];
@@ -569,11 +573,11 @@ k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, flo
     const size_t N = (size_t)P.nx * P.ny * P.nz;
     read_tile<S, FRC, ML, FX, ROW>(P, fin, phi, blockIdx.x, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
                                    [&](int z, const Macro &m, double ph, const RowMarch<ROW> &R) {
-        R.put(rho, z, m.rho);
-        R.put(pr, z, (P.p0 + m.dp) * m.rho * (1.0f / 3.0f));
+        R.template put<ROW>(rho, z, m.rho);
+        R.template put<ROW>(pr, z, (P.p0 + m.dp) * m.rho * (1.0f / 3.0f));
 #pragma unroll
-        for (int a = 0; a < 3; a++) R.put(u ? u + a * N : u, z, m.u[a]);
-        R.put(phi_out, z, ph);
+        for (int a = 0; a < 3; a++) R.template put<ROW>(u ? u + a * N : u, z, m.u[a]);
+        R.template put<ROW>(phi_out, z, ph);
     });
 }
 
