@@ -241,8 +241,9 @@ int lbm_harvest(lbm_handle *h, const double *centers, const double *radii, int n
 
 /* ------------------------------------------------------------------ batches
  * Many independent boxes advanced together: one persistent kernel launch per
- * time step takes work items (box, xy tile, z chunk) from a queue, so boxes of
- * uneven size share the GPU without one launch each; steps are replayed from
+ * time step (two for a large batch that mixes boxes with nx a multiple of 64 and
+ * others, which want other stores) takes work items (box, xy tile, z chunk) from a
+ * queue, so boxes of uneven size share the GPU without one launch each; steps are replayed from
  * a captured HIP graph.  Not in the paper (its runs are one box per job); it
  * is the ensemble mode of this library.  A box advanced in a batch gives
  * bit-identical fields to the same box advanced alone with lbm_step.
@@ -268,7 +269,7 @@ size_t lbm_batch_bytes(int n);
 int lbm_batch_create(lbm_batch **out, lbm_handle *const *members, int n, void *d_table, size_t table_bytes);
 
 /* Advance every member by nsteps (>= 0), asynchronously on the members' stream.
- * Pairs of steps replay a captured graph of two launches.  LBM_ESTATE if an
+ * Pairs of steps replay a captured graph of their launches.  LBM_ESTATE if an
  * MLP member has no weights. */
 int lbm_batch_step(lbm_batch *b, int64_t nsteps);
 

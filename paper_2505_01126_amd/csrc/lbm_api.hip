@@ -140,19 +140,29 @@ const char *validate(const lbm_config *c)
 
 }  // namespace
 
+// Members m0 .. m0 + n - 1 of a batch, stepped by one launch with one store policy.
+struct Group {
+    int m0 = 0, n = 0;
+    bool nt = false;
+    int grid = 0;   // persistent grid of the step kernel
+    int items = 0;  // work items of the launch: it has no more workgroups
+};
+
 struct lbm_batch {
-    std::vector<lbm_handle *> m;
+    std::vector<lbm_handle *> m;  // those with nx a multiple of 64 first
     std::vector<int> cur0;        // members' buffer parity when the tables were built
     std::vector<lbm::Params> P;   // per-member parameters (the batch's own z-chunk)
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;  // private stream the step-pair graph is recorded on
     char *table = nullptr;
     size_t off_tab = 0, off_buf = 0, off_first = 0, off_counter = 0;
-    int storage = 0, grid = 0, parity = 0, tile = 64;
-    bool tp = false, frc = false, ml = false, fix = false, rk3 = false, phys = false, dirty = true, nt = false;
+    int storage = 0, parity = 0, tile = 64;
+    bool tp = false, frc = false, ml = false, fix = false, rk3 = false, phys = false, dirty = true;
     int grid_ac = 0;  // persistent grid of the Runge-Kutta stage kernel
     int grid_ml = 0;  // persistent grid of the learned-curvature pass
-    int items = 0;    // work items of a launch: no launch has more workgroups
+    int items = 0;    // work items of those two: no launch has more workgroups
+    Group group[2];   // the step's launches
+    int groups = 1;
     hipGraphExec_t exec = nullptr;
     std::string err;
 
@@ -529,23 +539,37 @@ BatchOffsets batch_offsets(int n)
     o.first = off;
     off = align_up(off + sizeof(uint32_t) * ((size_t)n + 1));
     o.counter = off;
-    off = align_up(off + sizeof(uint32_t) * 4 * lbm::QCOUNTERS);  // queue counters of the four kernel kinds
+    // queue counters of the four kernel kinds, and of the step's second group
+    off = align_up(off + sizeof(uint32_t) * 5 * lbm::QCOUNTERS);
     o.total = off;
     return o;
 }
 
-// Non-temporal stores where every row of the 64-wide tiles fills whole
-// 128-byte lines in every member, and the populations outgrow the 256 MB
-// Infinity Cache: below that the next step reads them from it (64^3 FP32: 25.5
-// us with cached stores, 28.1 non-temporal; 128^3: 142 and 134 us).
-bool nt_stores(const lbm_batch *b)
+// The step's launches and their store policy.  Non-temporal stores pay for the
+// boxes whose tile rows fill whole 128-byte lines, once the populations outgrow the
+// 256 MB Infinity Cache: below that the next step reads them from it (64^3 FP32:
+// 25.5 us with cached stores, 28.1 non-temporal; 128^3: 142 and 134 us).  A batch
+// of both kinds of box, FP32 two-phase: where the whole-line ones hold nine tenths
+// of the sites, all go that way (320^3 and 100^3: 1.77 ms, 1.89 all cached); where they
+// hold a quarter or more, they get a launch of their own (two of 256^3 and four of
+// 150^3: 2.93 ms, 3.18 all cached, 3.23 all non-temporal); below that all are cached
+// (128^3 and four of 200^3: 2.66 ms, 2.70 in two launches).
+void choose_groups(lbm_batch *b, int tile)
 {
-    double bytes = 0.0;
+    const int n = (int)b->m.size();
+    double bytes = 0.0, lines = 0.0;
+    int nl = 0;  // members with nx a multiple of 64: the first ones
     for (const lbm_handle *h : b->m) {
-        if (h->cfg.nx % 64 != 0) return false;
-        bytes += 54.0 * (double)elem_bytes(h->cfg.storage) * h->cfg.nx * h->cfg.ny * h->cfg.nz;
+        const double v = 54.0 * (double)elem_bytes(h->cfg.storage) * h->cfg.nx * h->cfg.ny * h->cfg.nz;
+        bytes += v;
+        if (h->cfg.nx % 64 != 0) continue;
+        lines += v;
+        nl++;
     }
-    return bytes > 256e6;
+    if ((size_t)tile * elem_bytes(b->storage) % 128 != 0 || bytes <= 256e6) lines = 0.0;
+    b->groups = lines >= 0.25 * bytes && lines < 0.9 * bytes ? 2 : 1;
+    b->group[0] = Group{0, b->groups == 2 ? nl : n, lines >= 0.25 * bytes};
+    b->group[1] = Group{nl, n - nl, false};
 }
 
 // Tile width where none is asked for: 64 sites, or 32 (two rows per wave) where
@@ -574,16 +598,17 @@ int default_tile(const lbm_batch *b)
 // checks and stages every item, 7.25 at 16, 7.15 at 32; FP16: 4.61 at 32, 4.79
 // at 16; single phase, which has no prologue: FP32 5.29 ms at 2, 5.51 at 8, FP16
 // 3.00 at 4).
-int default_zchunk(const lbm_batch *b, int tile, int slots)
+int default_zchunk(const lbm_batch *b, const Group &g, int tile)
 {
+    const int slots = g.grid;
     const bool half = b->storage != LBM_STORE_F32;
     const int lo = b->tp ? 1 : 2, hi = b->tp ? (half || b->ml ? 32 : 16) : (half ? 4 : 2);
     int best = lo;
     double cost = 0.0;
     for (int c = lo; c <= hi; c++) {
         double items = 0.0;
-        for (const lbm_handle *h : b->m) {
-            lbm::Params P = h->P;
+        for (int i = g.m0; i < g.m0 + g.n; i++) {
+            lbm::Params P = b->P[i];
             set_tiling(P, tile, c);
             items += P.nblocks;
         }
@@ -630,8 +655,9 @@ int batch_upload(lbm_batch *b)
         first[i + 1] = first[i] + (uint32_t)b->P[i].nblocks;
     }
     b->items = (int)first[n];
+    for (Group &g : b->group) g.items = (int)(first[g.m0 + g.n] - first[g.m0]);
     // all queue counters start at zero (each launch clears the other parity's counters)
-    hipError_t e = hipMemsetAsync(b->d_counter(), 0, 4 * lbm::QCOUNTERS * sizeof(uint32_t), b->stream);
+    hipError_t e = hipMemsetAsync(b->d_counter(), 0, 5 * lbm::QCOUNTERS * sizeof(uint32_t), b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_tab(), b->P.data(), sizeof(lbm::Params) * n, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
@@ -652,26 +678,28 @@ int batch_upload(lbm_batch *b)
 int choose_tiling(lbm_batch *b, int tile, int zchunk)
 {
     if (tile == 0) tile = default_tile(b);
-    const bool nt = nt_stores(b);
-    const int grid = lbm::batch_grid(b->storage, b->tp, b->frc, b->ml, b->fix, b->phys, tile, nt);
+    choose_groups(b, tile);
     const int grid_ac = b->rk3 ? lbm::ac_stage_grid(tile) : 1;
     const int grid_ml = b->ml ? lbm::mlp_pass_grid(b->fix, tile) : 1;
-    if (grid <= 0 || grid_ac <= 0 || grid_ml <= 0) return b->fail(LBM_EHIP, "occupancy query failed");
-    const int zc = zchunk > 0 ? zchunk : default_zchunk(b, tile, grid);
-    for (size_t i = 0; i < b->m.size(); i++) {
-        const lbm_config &c = b->m[i]->cfg;
-        if (zchunk > 0) {
-            set_tiling(b->P[i], tile, zchunk);
-        } else if (c.zchunk > 0) {
-            set_tiling(b->P[i], tile, c.zchunk);
-        } else {  // as few items as zc gives, of even length
-            const int gz = (c.nz + zc - 1) / zc;
-            set_tiling(b->P[i], tile, (c.nz + gz - 1) / gz);
+    if (grid_ac <= 0 || grid_ml <= 0) return b->fail(LBM_EHIP, "occupancy query failed");
+    for (int k = 0; k < b->groups; k++) {
+        Group &g = b->group[k];
+        g.grid = lbm::batch_grid(b->storage, b->tp, b->frc, b->ml, b->fix, b->phys, tile, g.nt);
+        if (g.grid <= 0) return b->fail(LBM_EHIP, "occupancy query failed");
+        const int zc = zchunk > 0 ? zchunk : default_zchunk(b, g, tile);
+        for (int i = g.m0; i < g.m0 + g.n; i++) {
+            const lbm_config &c = b->m[i]->cfg;
+            if (zchunk > 0) {
+                set_tiling(b->P[i], tile, zchunk);
+            } else if (c.zchunk > 0) {
+                set_tiling(b->P[i], tile, c.zchunk);
+            } else {  // as few items as zc gives, of even length
+                const int gz = (c.nz + zc - 1) / zc;
+                set_tiling(b->P[i], tile, (c.nz + gz - 1) / gz);
+            }
         }
     }
     b->tile = tile;
-    b->nt = nt;
-    b->grid = grid;
     b->grid_ac = grid_ac;
     b->grid_ml = grid_ml;
     b->dirty = true;
@@ -685,16 +713,20 @@ int choose_tiling(lbm_batch *b, int tile, int zchunk)
 hipError_t batch_launch(lbm_batch *b, int parity, hipStream_t s)
 {
     const int n = (int)b->m.size();
-    const int grid = std::min(b->grid, b->items), grid_ac = std::min(b->grid_ac, b->items),
-              grid_ml = std::min(b->grid_ml, b->items);
+    const int grid_ac = std::min(b->grid_ac, b->items), grid_ml = std::min(b->grid_ml, b->items);
     if (b->ml) {
         hipError_t e = lbm::launch_mlp_pass_batch(b->d_tab(), b->d_buf(3, parity), b->d_first(), n,
                                                   b->d_counter() + 3 * lbm::QCOUNTERS, parity, b->fix, b->tile,
                                                   grid_ml, s);
         if (e != hipSuccess) return e;
     }
-    hipError_t e = lbm::launch_step_batch(b->d_tab(), b->d_buf(0, parity), b->d_first(), n, b->d_counter(), parity,
-                                          b->storage, b->tp, b->frc, b->ml, b->fix, b->phys, b->tile, b->nt, grid, s);
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < b->groups && e == hipSuccess; k++) {
+        const Group &g = b->group[k];
+        e = lbm::launch_step_batch(b->d_tab() + g.m0, b->d_buf(0, parity) + g.m0, b->d_first() + g.m0, g.n,
+                                   b->d_counter() + (k ? 4 : 0) * lbm::QCOUNTERS, parity, b->storage, b->tp, b->frc,
+                                   b->ml, b->fix, b->phys, b->tile, g.nt, std::min(g.grid, g.items), s);
+    }
     if (e == hipSuccess && b->rk3)
         e = lbm::launch_ac_stage_batch(b->d_tab(), b->d_buf(1, parity), b->d_first(), n,
                                        b->d_counter() + 1 * lbm::QCOUNTERS, parity, 0.75, 0.25, b->tile, grid_ac, s);
@@ -759,6 +791,7 @@ int lbm_batch_create(lbm_batch **out, lbm_handle *const *members, int n, void *d
     }
     lbm_batch *b = new (std::nothrow) lbm_batch();
     if (!b) return bad(LBM_EINVAL, "out of host memory");
+    std::stable_partition(m.begin(), m.end(), [](const lbm_handle *h) { return h->cfg.nx % 64 == 0; });
     b->m = m;
     b->cur0.assign(n, 0);
     b->stream = h0->stream;

@@ -167,7 +167,7 @@ template <class T> __device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, 
 // reads them before the next launch, by which time a 512^3 state has long left
 // L2 and the Infinity Cache, so caching them only evicts input lines that
 // neighbouring work items still fetch (measured 2-4 % faster per step on
-// 512^3).  The step uses them only where every tile row covers whole 128-byte
+// 512^3).  The step uses them only where the tile rows cover whole 128-byte
 // lines (a partial line written past the caches measured slower: a batch of
 // boxes with edges 32-96, 8 %) and the populations exceed the Infinity Cache,
 // which otherwise holds them for the next step.  Loads keep the default
@@ -1309,8 +1309,8 @@ __device__ __forceinline__ void pass_tile(const Params &P, const Buffers &B, con
 // ------------------------------------------------------------ work queue
 // The persistent loop of a batched launch over the boxes of a batch: a
 // workgroup takes the next work item from one queue counter per launch, so the
-// load stays balanced to the last item; item k belongs to the box b with
-// first[b] <= k < first[b + 1].  The counter of this launch is counter[parity];
+// load stays balanced to the last item; item k, counted from first[0], belongs to the
+// box b with first[b] <= k < first[b + 1].  The counter of this launch is counter[parity];
 // the launch clears the other one for the next launch on the stream.
 // body(b, item within the box) runs with every thread of the workgroup.
 // (Per-die queues, each die draining a contiguous range of items first so that
@@ -1329,17 +1329,18 @@ __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ first, i
 {
     __shared__ uint32_t s_item;
     const int tid = threadIdx.y * TW + threadIdx.x;
-    const uint32_t total = first[nbox];
+    const uint32_t item0 = first[0], total = first[nbox] - item0;
     if (blockIdx.x == 0 && tid == 0) counter[parity ^ 1] = 0u;
     for (uint32_t item = blockIdx.x; item < total;) {
+        const uint32_t k = item0 + item;
         int lo = 0, hi = nbox - 1;  // last box with first[b] <= item
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (first[mid] <= item) lo = mid;
+            if (first[mid] <= k) lo = mid;
             else hi = mid - 1;
         }
         const int b = __builtin_amdgcn_readfirstlane(lo);
-        body(b, item - first[b]);
+        body(b, k - first[b]);
         if (total <= gridDim.x) break;
         if (tid == 0) s_item = gridDim.x + atomicAdd(&counter[parity], 1u);
         __syncthreads();  // the item's LDS traffic is over
@@ -1434,11 +1435,13 @@ k_step_batch(const Params *__restrict__ tab, const Buffers *__restrict__ buf, co
 // Occupancy-sized persistent grid and launch of the step kernel for one
 // population storage S; each storage is instantiated in a translation unit
 // of its own (lbm_step_s0/s1/s2.hip) so that the build compiles them in parallel.
-// nt: non-temporal stores (tile 64 only)
+// nt: non-temporal stores (tile 64, and with FP32 populations 32, whose rows are whole lines too)
 #define LBM_STEP_TILE(S_, TP_, F_, M_, X_, H_, CALL)                                   \
     {                                                                                  \
-        if (tile == 32) CALL((k_step_batch<S_, TP_, F_, M_, 32, X_, H_, false>))       \
-        else if (nt) CALL((k_step_batch<S_, TP_, F_, M_, 64, X_, H_, true>))           \
+        if (tile == 32) {                                                              \
+            if (S_ == 0 && nt) CALL((k_step_batch<S_, TP_, F_, M_, 32, X_, H_, S_ == 0>)) \
+            else CALL((k_step_batch<S_, TP_, F_, M_, 32, X_, H_, false>))              \
+        } else if (nt) CALL((k_step_batch<S_, TP_, F_, M_, 64, X_, H_, true>))         \
         else CALL((k_step_batch<S_, TP_, F_, M_, 64, X_, H_, false>))                  \
     }
 template <int S>
