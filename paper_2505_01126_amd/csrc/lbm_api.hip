@@ -572,19 +572,32 @@ void choose_groups(lbm_batch *b, int tile)
     b->group[1] = Group{nl, n - nl, false};
 }
 
-// Tile width where none is asked for: 64 sites, or 32 (two rows per wave) where
-// that saves a fifth or more of the sites that the tiles cover past the boxes'
-// edges (96^3 single phase, FP32: 43 us against 49; nx = 150, which saves a
-// sixth: 290 us against 275).
+// Tile width where none is asked for: 64 x 4 sites, or 32 x 8 (two rows per wave)
+// where that covers so much less past the boxes' edges that the dearer lanes of the
+// narrow tile pay.  Their price is a quarter more where rows start on every 16th site
+// (FP32: 64 bytes; 96^3 single phase: 43 us against 49; nx = 150, which saves a sixth:
+// 290 us against 275), and half as much again where they do not (90 x 300 x 300
+// two-phase: 0.82 ms against 0.72).  16-bit two-phase populations and the network
+// are bound by their instructions rather than by those lines: a quarter on
+// every 8th site (FP16, 72^3, thirty boxes: 0.69 ms against 0.74), three tenths
+// elsewhere (90^3, sixteen: 0.78 against 0.68; learned curvature, FP32, 90 x 300 x
+// 300: 0.97 and 1.08).  The Runge-Kutta stages are so throughout (66 x 200 x 200:
+// 0.57 and 0.65 ms).
+double narrow_price(const lbm_batch *b, int nx)
+{
+    if (b->rk3) return 1.25;
+    if (b->ml || (b->tp && b->storage != LBM_STORE_F32)) return nx % 8 == 0 ? 1.25 : 1.3;
+    return nx % 16 == 0 ? 1.25 : 1.5;
+}
 int default_tile(const lbm_batch *b)
 {
     double w64 = 0.0, w32 = 0.0;
     for (const lbm_handle *h : b->m) {
-        const double rows = (double)h->cfg.ny * h->cfg.nz;
-        w64 += rows * ((h->cfg.nx + 63) / 64 * 64);
-        w32 += rows * ((h->cfg.nx + 31) / 32 * 32);
+        const int nx = h->cfg.nx, ny = h->cfg.ny;
+        w64 += (double)h->cfg.nz * ((nx + 63) / 64 * 64) * ((ny + 3) / 4 * 4);
+        w32 += (double)h->cfg.nz * ((nx + 31) / 32 * 32) * ((ny + 7) / 8 * 8) * narrow_price(b, nx);
     }
-    return 5.0 * w32 <= 4.0 * w64 ? 32 : 64;
+    return w32 <= w64 ? 32 : 64;
 }
 
 // Planes per work item where none is asked for: the length that brings the
