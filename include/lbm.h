@@ -275,11 +275,13 @@ int lbm_batch_step(lbm_batch *b, int64_t nsteps);
 
 /* Autotuner of the work decomposition: time steps_per_candidate (>= 1) steps,
  * after one warm-up step, for each workgroup tile (64 x 4 or 32 x 8 sites:
- * one or two x-rows per wave) and z-chunk length in {8, 16, 32, 64}, and keep
- * the fastest, cached per set of member shapes for the life of the process (a
- * cached set is not timed again).  The timed steps advance the members like
- * lbm_batch_step; results do not depend on the decomposition.  Waits for the
- * stream.  *tile_out and *zchunk_out (host, may be NULL) get the choice. */
+ * one or two x-rows per wave) and z-chunk length in {8, 16, 32, 64}, and take the
+ * fastest, or the decomposition that lbm_batch_create chose where that is no slower
+ * (small boxes want shorter chunks), cached per set of member shapes for the life
+ * of the process (a cached set is not timed again).  The steps of the eight
+ * candidates advance the members like lbm_batch_step, the final comparison does not;
+ * results do not depend on the decomposition.  Waits for the stream.  *tile_out
+ * and *zchunk_out (host, may be NULL) get the fastest of the eight. */
 int lbm_batch_tune(lbm_batch *b, int steps_per_candidate, int *tile_out, int *zchunk_out);
 
 /* Set the work decomposition by hand: tile 64 (64 x 4 sites) or 32 (32 x 8),

@@ -634,8 +634,6 @@ int default_zchunk(const lbm_batch *b, const Group &g, int tile)
     return best;
 }
 
-int choose_tiling(lbm_batch *b, int tile, int zchunk);
-
 // Upload the parameter table, both parities of the buffer table and the
 // work-item prefix sums for the members' current state.
 int batch_upload(lbm_batch *b)
@@ -722,14 +720,14 @@ int choose_tiling(lbm_batch *b, int tile, int zchunk)
 // one time step of the batch with the given parity of the buffer tables: with
 // the learned curvature its network pass, then the step kernel, then, with the
 // Runge-Kutta phase-field update, its second and third stages (Shu-Osher
-// coefficients 3/4, 1/4 and 1/3, 2/3)
-hipError_t batch_launch(lbm_batch *b, int parity, hipStream_t s)
+// coefficients 3/4, 1/4 and 1/3, 2/3).  queue: the parity of the queue counters.
+hipError_t batch_launch(lbm_batch *b, int parity, int queue, hipStream_t s)
 {
     const int n = (int)b->m.size();
     const int grid_ac = std::min(b->grid_ac, b->items), grid_ml = std::min(b->grid_ml, b->items);
     if (b->ml) {
         hipError_t e = lbm::launch_mlp_pass_batch(b->d_tab(), b->d_buf(3, parity), b->d_first(), n,
-                                                  b->d_counter() + 3 * lbm::QCOUNTERS, parity, b->fix, b->tile,
+                                                  b->d_counter() + 3 * lbm::QCOUNTERS, queue, b->fix, b->tile,
                                                   grid_ml, s);
         if (e != hipSuccess) return e;
     }
@@ -737,16 +735,35 @@ hipError_t batch_launch(lbm_batch *b, int parity, hipStream_t s)
     for (int k = 0; k < b->groups && e == hipSuccess; k++) {
         const Group &g = b->group[k];
         e = lbm::launch_step_batch(b->d_tab() + g.m0, b->d_buf(0, parity) + g.m0, b->d_first() + g.m0, g.n,
-                                   b->d_counter() + (k ? 4 : 0) * lbm::QCOUNTERS, parity, b->storage, b->tp, b->frc,
+                                   b->d_counter() + (k ? 4 : 0) * lbm::QCOUNTERS, queue, b->storage, b->tp, b->frc,
                                    b->ml, b->fix, b->phys, b->tile, g.nt, std::min(g.grid, g.items), s);
     }
     if (e == hipSuccess && b->rk3)
         e = lbm::launch_ac_stage_batch(b->d_tab(), b->d_buf(1, parity), b->d_first(), n,
-                                       b->d_counter() + 1 * lbm::QCOUNTERS, parity, 0.75, 0.25, b->tile, grid_ac, s);
+                                       b->d_counter() + 1 * lbm::QCOUNTERS, queue, 0.75, 0.25, b->tile, grid_ac, s);
     if (e == hipSuccess && b->rk3)
         e = lbm::launch_ac_stage_batch(b->d_tab(), b->d_buf(2, parity), b->d_first(), n,
-                                       b->d_counter() + 2 * lbm::QCOUNTERS, parity, 1.0 / 3.0, 2.0 / 3.0, b->tile,
+                                       b->d_counter() + 2 * lbm::QCOUNTERS, queue, 1.0 / 3.0, 2.0 / 3.0, b->tile,
                                        grid_ac, s);
+    return e;
+}
+
+// two steps of the batch recorded as a graph, on the private stream (the members'
+// stream may be the legacy default stream, which cannot be captured): the second
+// from where the first ends, or (again) both from the same state
+hipError_t record_pair(lbm_batch *b, bool again, hipGraphExec_t *exec)
+{
+    hipGraph_t g = nullptr;
+    hipError_t e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        const hipError_t e0 = batch_launch(b, 0, 0, b->capture);
+        const hipError_t e1 = batch_launch(b, again ? 0 : 1, 1, b->capture);
+        e = hipStreamEndCapture(b->capture, &g);
+        if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1;
+    }
+    if (e == hipSuccess) e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
+    if (g) (void)hipGraphDestroy(g);
+    if (e != hipSuccess) *exec = nullptr;
     return e;
 }
 
@@ -759,8 +776,44 @@ void batch_advance(lbm_batch *b, int64_t k)
     b->parity ^= (int)(k & 1);
 }
 
+// Milliseconds of n steps with a decomposition (0, 0: the default), lowered in *ms
+// where they are fewer.  The members stay where they are: every step starts from
+// the present state and writes the buffers that the next real step writes again.
+// (Reading the same buffers every time helps the caches a little, so only such
+// times are comparable with each other: 128^3.)
+int time_in_place(lbm_batch *b, int tile, int zchunk, int n, hipEvent_t e0, hipEvent_t e1, float *ms)
+{
+    if (int rc = choose_tiling(b, tile, zchunk)) return rc;
+    if (int rc = batch_upload(b)) return rc;
+    hipGraphExec_t pair = nullptr;
+    hipError_t e = batch_launch(b, 0, 0, b->stream);  // warm-up
+    if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
+    if (e == hipSuccess) e = batch_launch(b, 0, 1, b->stream);
+    if (e == hipSuccess && n > 2) e = record_pair(b, true, &pair);
+    for (int k = 2; k < n && e == hipSuccess; k += 2) e = hipGraphLaunch(pair, b->stream);
+    if (e == hipSuccess && n % 2 == 0) e = batch_launch(b, 0, 0, b->stream);
+    if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
+    if (b->ml)  // the flags are those of the state after the step: every item to the network again
+        for (lbm_handle *h : b->m)
+            if (e == hipSuccess)
+                e = hipMemsetAsync(h->iflag(), 1, (size_t)lbm::flag_segments(h->cfg.nx) * h->cfg.ny * h->cfg.nz,
+                                   b->stream);
+    const hipError_t w = hipStreamSynchronize(b->stream);
+    if (e == hipSuccess) e = w;
+    float t = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
+    if (pair) (void)hipGraphExecDestroy(pair);
+    b->dirty = true;  // the queue counters
+    *ms = std::min(*ms, t);
+    return b->hip(e, "timing in place");
+}
+
+struct Tuned {
+    int tile, zchunk;  // the fastest candidate
+    bool keep;         // the default is faster still
+};
 std::mutex g_tune_mu;
-std::map<std::string, std::pair<int, int>> g_tune_cache;  // member shapes and kernel flags -> (tile, z-chunk)
+std::map<std::string, Tuned> g_tune_cache;  // by member shapes and kernel flags
 thread_local std::string g_batch_err;
 
 }  // namespace
@@ -854,34 +907,18 @@ int lbm_batch_step(lbm_batch *b, int64_t nsteps)
         if (int rc = batch_upload(b)) return rc;
     int64_t left = nsteps;
     if (b->parity == 1) {  // realign so that graph replays start at parity 0
-        if (int rc = b->hip(batch_launch(b, 1, b->stream), "batch kernel")) return rc;
+        if (int rc = b->hip(batch_launch(b, 1, 1, b->stream), "batch kernel")) return rc;
         batch_advance(b, 1);
         left--;
     }
-    if (left >= 2 && !b->exec) {
-        hipGraph_t g = nullptr;
-        // recorded on the private stream (the members' stream may be the
-        // legacy default stream, which cannot be captured), replayed on theirs
-        hipError_t e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            hipError_t e0 = batch_launch(b, 0, b->capture);
-            hipError_t e1 = batch_launch(b, 1, b->capture);
-            e = hipStreamEndCapture(b->capture, &g);
-            if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1;
-        }
-        if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
-        if (g) (void)hipGraphDestroy(g);
-        if (e != hipSuccess) {
-            b->exec = nullptr;
-            return b->hip(e, "batch graph capture");
-        }
-    }
+    if (left >= 2 && !b->exec)
+        if (int rc = b->hip(record_pair(b, false, &b->exec), "batch graph capture")) return rc;
     for (; left >= 2; left -= 2) {
         if (int rc = b->hip(hipGraphLaunch(b->exec, b->stream), "batch graph launch")) return rc;
         batch_advance(b, 2);
     }
     if (left == 1) {
-        if (int rc = b->hip(batch_launch(b, 0, b->stream), "batch kernel")) return rc;
+        if (int rc = b->hip(batch_launch(b, 0, 0, b->stream), "batch kernel")) return rc;
         batch_advance(b, 1);
     }
     return LBM_OK;
@@ -893,21 +930,19 @@ int lbm_batch_tune(lbm_batch *b, int steps_per_candidate, int *tile_out, int *zc
     if (steps_per_candidate < 1) return b->fail(LBM_EINVAL, "steps_per_candidate must be >= 1");
     std::vector<std::string> shapes;
     for (lbm_handle *h : b->m)
-        shapes.push_back(std::to_string(h->cfg.nx) + "x" + std::to_string(h->cfg.ny) + "x" + std::to_string(h->cfg.nz));
+        shapes.push_back(std::to_string(h->cfg.nx) + "x" + std::to_string(h->cfg.ny) + "x" + std::to_string(h->cfg.nz) +
+                         (h->cfg.zchunk > 0 ? "/" + std::to_string(h->cfg.zchunk) : ""));  // the default depends on it
     std::sort(shapes.begin(), shapes.end());
     std::string key = std::to_string(b->storage) + (b->tp ? "t" : "s") + (b->frc ? "f" : "-") + (b->ml ? "m" : "d") + (b->fix ? "q" : "") + (b->rk3 ? "r" : "") + (b->phys ? "g" : "");
     for (const std::string &sh : shapes) key += "," + sh;
     auto apply = [&](int tile, int zc) -> int { return lbm_batch_set_tiling(b, tile, zc); };
-    int best_tile = -1, best_zc = -1;
+    Tuned best{-1, -1, false};
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(key);
-        if (it != g_tune_cache.end()) {
-            best_tile = it->second.first;
-            best_zc = it->second.second;
-        }
+        if (it != g_tune_cache.end()) best = it->second;
     }
-    if (best_tile < 0) {
+    if (best.tile < 0) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (int rc = b->hip(hipEventCreate(&e0), "event")) return rc;
         if (int rc = b->hip(hipEventCreate(&e1), "event")) {
@@ -926,23 +961,29 @@ int lbm_batch_tune(lbm_batch *b, int steps_per_candidate, int *tile_out, int *zc
                 if ((rc = b->hip(hipEventSynchronize(e1), "event"))) break;
                 float ms = 0.f;
                 if ((rc = b->hip(hipEventElapsedTime(&ms, e0, e1), "event"))) break;
-                if (best_tile < 0 || ms < best_ms) {
-                    best_tile = tile;
-                    best_zc = zc;
+                if (best.tile < 0 || ms < best_ms) {
+                    best = Tuned{tile, zc, false};
                     best_ms = ms;
                 }
             }
             if (rc) break;
         }
+        float default_ms = INFINITY;
+        best_ms = INFINITY;
+        for (int k = 0; k < 2; k++) {  // the fastest and the default, in turn
+            if (!rc) rc = time_in_place(b, best.tile, best.zchunk, steps_per_candidate, e0, e1, &best_ms);
+            if (!rc) rc = time_in_place(b, 0, 0, steps_per_candidate, e0, e1, &default_ms);
+        }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (rc) return rc;
+        best.keep = default_ms <= best_ms;
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tune_cache[key] = {best_tile, best_zc};
+        g_tune_cache[key] = best;
     }
-    if (int rc = apply(best_tile, best_zc)) return rc;
-    if (tile_out) *tile_out = best_tile;
-    if (zchunk_out) *zchunk_out = best_zc;
+    if (int rc = best.keep ? choose_tiling(b, 0, 0) : apply(best.tile, best.zchunk)) return rc;
+    if (tile_out) *tile_out = best.tile;
+    if (zchunk_out) *zchunk_out = best.zchunk;
     return LBM_OK;
 }
 

@@ -222,7 +222,7 @@ def lbm_batch_step(b, nsteps):
 
 
 def lbm_batch_tune(b, steps_per_candidate):
-    """Returns (tile width, z-chunk length)."""
+    """Returns (tile width, z-chunk length) of the fastest candidate."""
     tile = C.c_int(0)
     zc = C.c_int(0)
     _check_batch(load_library().lbm_batch_tune(b, int(steps_per_candidate), C.byref(tile), C.byref(zc)), b,
@@ -412,8 +412,9 @@ class Batch:
         lbm_batch_step(self.b, n)
 
     def tune(self, steps_per_candidate=4):
-        """Pick the tile width and z-chunk length by timing; returns (tile, zchunk)
-        (the timed steps advance the lattices)."""
+        """Pick the work decomposition by timing: eight pairs of tile width and z-chunk
+        length, whose timed steps advance the lattices, and the default, which is kept
+        where it is no slower.  Returns the fastest of the eight, (tile, zchunk)."""
         return lbm_batch_tune(self.b, steps_per_candidate)
 
     def set_tiling(self, tile, zchunk):
