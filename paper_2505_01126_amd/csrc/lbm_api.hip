@@ -299,7 +299,6 @@ int lbm_init(lbm_handle **out, const lbm_config *cfg, void *d_ws, size_t ws_byte
     P.mlp = h->ws + L.mlp;
     P.frow = nullptr;
     P.fx = nullptr;
-    set_tiling(P, lbm::TX, cfg->zchunk > 0 ? cfg->zchunk : cfg->nz);  // a batch chooses its own
 
     if (cfg->n_modes > 0) {
         // The body-force tables are formed on the device (k_forcing) from the
