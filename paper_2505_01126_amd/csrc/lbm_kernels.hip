@@ -100,11 +100,6 @@ template <bool ROW> struct RowMarch {
     // base may be null: a buffer of no bytes, whose stores the hardware drops.
     // Its scalar offset is zero then: the range check is vector offset >= bytes -
     // scalar offset, a difference that must not go below zero.
-    // NT: non-temporal.  The fields of a read-out by rows go that way (512^3: 4.00
-    // ms against 4.13; read again at once, 256^3: 602 us either way).  Where rows
-    // end inside a line, and for the initial phi and u, which the first step reads,
-    // they go through the caches (150 x 141 x 203, FP32 read-out and a pass over u
-    // and phi: 161 us, 172 non-temporal; set-up of 129 x 130 x 131: 160 and 172 us).
     template <bool NT, class E> __device__ __forceinline__ void put(E *base, int z, E v) const
     {
         const uint32_t bytes = base ? plane * (uint32_t)sizeof(E) : 0u;
@@ -149,6 +144,7 @@ int even_chunk(const Params &p, int wx)
 struct Plan {
     bool sites;
     int wx, chunk;
+    bool nt = false;  // a march's fields are stored non-temporally
 };
 // The plane's sites fill less than `tenths` tenths of the lanes that a march puts
 // on it: 256 lanes walk z for 64 sites of 8 x 8, 512 for 289 of 17 x 17.
@@ -156,13 +152,20 @@ bool thin(const Params &p, int tenths)
 {
     return (int64_t)p.nx * p.ny * 10 < march_tiles(p, 0) * NTHREADS * tenths;
 }
+// Fields too large to stay in the caches until they are read are stored
+// non-temporally.  The initial phi and u of a box from 1.18 M sites on: set-up and
+// first step of 400 x 400 x 60 1.14 ms, 1.19 cached; of 32^3 to 64^3 up to 10 us
+// less cached.  The fields of a read-out from 256 MB on, and those of rows, which are
+// whole lines: FP32 read-out of 250^3 and a pass over u and phi 0.56 ms, 0.62 cached; of
+// 129 x 130 x 131 82 and 79 us; of 512^3 alone, 4.00 ms, 4.13 cached.
+bool large(const Params &p, int64_t sites) { return (int64_t)p.nx * p.ny * p.nz >= sites; }
 // Set-up.  By sites on thin planes (8 x 8 x 65536: 321 us against 570; 17 x 17 x
 // 4000: 127 and 140); 20 x 20, which fills 0.78 of the lanes, is even, and full
 // planes gain by the march (256^3: 0.80 against 1.1 ms).
 Plan plan_init(const Params &p)
 {
     const int wx = march_wx(p, false);
-    return {thin(p, 6), wx, march_chunk(p, wx)};
+    return {thin(p, 6), wx, march_chunk(p, wx), large(p, (int64_t)NTHREADS * 6 * RED_BLOCKS)};
 }
 // Read-out (fields) and reduction.  In single phase there is no stencil whose sums
 // a march could carry, and a thread per site reads its 27 populations as fast or
@@ -181,12 +184,13 @@ Plan plan_read(const Params &p, int storage, bool fields)
 {
     if (!p.two_phase) return {true, 0, 0};
     const int wx = march_wx(p, storage != 0);
+    const bool nt = wx || large(p, 256000000 / 28);
     if (p.curv_mode == 1) {
         const int c = march_chunk(p, wx, 6);
-        return {thin(p, 8) || (fields && c < 2), wx, c};
+        return {thin(p, 8) || (fields && c < 2), wx, c, nt};
     }
     const bool few = !fields && (int64_t)p.nx * p.ny * p.nz <= 1 << 21;
-    return {thin(p, p.phi_fix ? 5 : 6), wx, few ? even_chunk(p, wx) : march_chunk(p, wx)};
+    return {thin(p, p.phi_fix ? 5 : 6), wx, few ? even_chunk(p, wx) : march_chunk(p, wx), nt};
 }
 uint32_t site_blocks(const Params &p) { return ((uint32_t)p.nx * p.ny * p.nz + NTHREADS - 1) / NTHREADS; }
 uint32_t march_items(const Params &p, int chunk, int wx)
@@ -277,7 +281,7 @@ __global__ void __launch_bounds__(NTHREADS) k_init_site(Params P, void *fout_, v
 // planes it enters (27 loads per site instead of 81): the sums of site z+1 and
 // z+2 are under way while those of z are completed, each in the order of the
 // velocities.
-template <int S, bool ROW>
+template <int S, bool ROW, bool NT>
 __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *phi_out, float *u_out,
                                                    const double *phi0, const double *u0, const double *ps0, int chunk,
                                                    int wx)
@@ -343,11 +347,11 @@ __global__ void __launch_bounds__(NTHREADS) k_init(Params P, void *fout_, void *
             bstore<T>(dst[CZ(i) + 1], R.vcol(1 - CY(i), 1 - CX(i)) * ES, ((uint32_t)i * plane + R.srow(1 - CY(i))) * ES,
                       Pop<S>::enc(h));
         });
-        if (P.phi_fix) R.template put<false>((int32_t *)phi_out, z, phi_to_fix(ph));
-        else R.template put<false>((double *)phi_out, z, ph);
+        if (P.phi_fix) R.template put<NT>((int32_t *)phi_out, z, phi_to_fix(ph));
+        else R.template put<NT>((double *)phi_out, z, ph);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-            R.template put<false>(u_out ? u_out + a * N : u_out, z, (float)u[a]);
+            R.template put<NT>(u_out ? u_out + a * N : u_out, z, (float)u[a]);
             u[a] = un[a];
             for (int b = 0; b < 3; b++) {
                 G[a][b] = Gn[a][b];
@@ -559,7 +563,7 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
     }
 }
 
-template <int S, bool FRC, bool ML, bool FX, bool ROW>
+template <int S, bool FRC, bool ML, bool FX, bool ROW, bool NT>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ML || !ROW ? 3 : 4)))
 k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, float *u, double *phi_out, int chunk, int wx)
 {
@@ -573,11 +577,11 @@ k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, flo
     const size_t N = (size_t)P.nx * P.ny * P.nz;
     read_tile<S, FRC, ML, FX, ROW>(P, fin, phi, blockIdx.x, chunk, wx, W, wv[ML ? threadIdx.x >> 6 : 0],
                                    [&](int z, const Macro &m, double ph, const RowMarch<ROW> &R) {
-        R.template put<ROW>(rho, z, m.rho);
-        R.template put<ROW>(pr, z, (P.p0 + m.dp) * m.rho * (1.0f / 3.0f));
+        R.template put<NT>(rho, z, m.rho);
+        R.template put<NT>(pr, z, (P.p0 + m.dp) * m.rho * (1.0f / 3.0f));
 #pragma unroll
-        for (int a = 0; a < 3; a++) R.template put<ROW>(u ? u + a * N : u, z, m.u[a]);
-        R.template put<ROW>(phi_out, z, ph);
+        for (int a = 0; a < 3; a++) R.template put<NT>(u ? u + a * N : u, z, m.u[a]);
+        R.template put<NT>(phi_out, z, ph);
     });
 }
 
@@ -835,18 +839,19 @@ hipError_t launch_init(const Params &p, int storage, void *fout, void *phi_out, 
     }
     const int wx = plan.wx, c = plan.chunk;
     const dim3 grid(march_items(p, c, wx));
-#define INIT(S_, R_) \
-    hipLaunchKernelGGL((k_init<S_, R_>), grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0, c, wx)
-    if (wx) {
-        if (storage == 0) INIT(0, true);
-        else if (storage == 1) INIT(1, true);
-        else INIT(2, true);
-    } else {
-        if (storage == 0) INIT(0, false);
-        else if (storage == 1) INIT(1, false);
-        else INIT(2, false);
+#define INIT_AS(S_, R_, NT_) \
+    hipLaunchKernelGGL((k_init<S_, R_, NT_>), grid, block, 0, s, p, fout, phi_out, u_out, phi0, u0, ps0, c, wx)
+#define INIT(S_)                                 \
+    {                                            \
+        if (wx) INIT_AS(S_, true, true);         \
+        else if (plan.nt) INIT_AS(S_, false, true); \
+        else INIT_AS(S_, false, false);          \
     }
+    if (storage == 0) INIT(0)
+    else if (storage == 1) INIT(1)
+    else INIT(2)
 #undef INIT
+#undef INIT_AS
     return hipGetLastError();
 }
 
@@ -949,10 +954,17 @@ hipError_t launch_moments(const Params &p, int storage, const void *fin, const v
     }
     const int wx = plan.wx, c = plan.chunk;
     const dim3 grid(march_items(p, c, wx));
-#define MARCH(S_, F_, M_, X_, R_) \
-    hipLaunchKernelGGL((k_moments<S_, F_, M_, X_, R_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out, c, wx)
+#define MARCH_AS(S_, F_, M_, X_, R_, NT_)                                                                           \
+    hipLaunchKernelGGL((k_moments<S_, F_, M_, X_, R_, NT_>), grid, block, 0, s, p, fin, phi, rho, pr, u, phi_out, c, \
+                       wx)
+#define MARCH(S_, F_, M_, X_, R_)                                \
+    do {                                                         \
+        if (R_ || plan.nt) MARCH_AS(S_, F_, M_, X_, R_, true);   \
+        else MARCH_AS(S_, F_, M_, X_, R_, R_);                   \
+    } while (0)
     LBM_DISPATCH(storage, tp, frc, ml, LBM_MARCH_CALL);
 #undef MARCH
+#undef MARCH_AS
     return hipGetLastError();
 }
 
