@@ -536,7 +536,8 @@ BatchOffsets batch_offsets(int n)
     o.buf = off;
     off = align_up(off + sizeof(lbm::Buffers) * 4 * 2 * (size_t)n);
     o.first = off;
-    off = align_up(off + sizeof(uint32_t) * ((size_t)n + 1));
+    // all members' prefix sums, and those of the step's second group from its own zero
+    off = align_up(off + sizeof(uint32_t) * 2 * ((size_t)n + 1));
     o.counter = off;
     // queue counters of the four kernel kinds, and of the step's second group
     off = align_up(off + sizeof(uint32_t) * 5 * lbm::QCOUNTERS);
@@ -639,7 +640,7 @@ int batch_upload(lbm_batch *b)
 {
     const int n = (int)b->m.size();
     std::vector<lbm::Buffers> buf(4 * 2 * (size_t)n, lbm::Buffers{});
-    std::vector<uint32_t> first((size_t)n + 1, 0u);
+    std::vector<uint32_t> first(2 * ((size_t)n + 1), 0u);
     for (int i = 0; i < n; i++) {
         lbm_handle *h = b->m[i];
         b->cur0[i] = h->cur;
@@ -666,6 +667,8 @@ int batch_upload(lbm_batch *b)
     }
     b->items = (int)first[n];
     for (Group &g : b->group) g.items = (int)(first[g.m0 + g.n] - first[g.m0]);
+    for (int i = 0; i < b->group[1].n; i++)
+        first[n + 2 + i] = first[n + 1 + i] + (uint32_t)b->P[b->group[1].m0 + i].nblocks;
     // all queue counters start at zero (each launch clears the other parity's counters)
     hipError_t e = hipMemsetAsync(b->d_counter(), 0, 5 * lbm::QCOUNTERS * sizeof(uint32_t), b->stream);
     if (e == hipSuccess)
@@ -674,7 +677,8 @@ int batch_upload(lbm_batch *b)
         e = hipMemcpyAsync(b->d_buf(), buf.data(), sizeof(lbm::Buffers) * 4 * 2 * n, hipMemcpyHostToDevice,
                            b->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(b->d_first(), first.data(), sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice, b->stream);
+        e = hipMemcpyAsync(b->d_first(), first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice,
+                           b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);  // host staging is released below
     if (e != hipSuccess) return b->hip(e, "batch table upload");
     b->parity = 0;
@@ -733,7 +737,7 @@ hipError_t batch_launch(lbm_batch *b, int parity, int queue, hipStream_t s)
     hipError_t e = hipSuccess;
     for (int k = 0; k < b->groups && e == hipSuccess; k++) {
         const Group &g = b->group[k];
-        e = lbm::launch_step_batch(b->d_tab() + g.m0, b->d_buf(0, parity) + g.m0, b->d_first() + g.m0, g.n,
+        e = lbm::launch_step_batch(b->d_tab() + g.m0, b->d_buf(0, parity) + g.m0, b->d_first() + (k ? n + 1 : 0), g.n,
                                    b->d_counter() + (k ? 4 : 0) * lbm::QCOUNTERS, queue, b->storage, b->tp, b->frc,
                                    b->ml, b->fix, b->phys, b->tile, g.nt, std::min(g.grid, g.items), s);
     }

@@ -1309,8 +1309,8 @@ __device__ __forceinline__ void pass_tile(const Params &P, const Buffers &B, con
 // ------------------------------------------------------------ work queue
 // The persistent loop of a batched launch over the boxes of a batch: a
 // workgroup takes the next work item from one queue counter per launch, so the
-// load stays balanced to the last item; item k, counted from first[0], belongs to the
-// box b with first[b] <= k < first[b + 1].  The counter of this launch is counter[parity];
+// load stays balanced to the last item; item k belongs to the box b with
+// first[b] <= k < first[b + 1].  The counter of this launch is counter[parity];
 // the launch clears the other one for the next launch on the stream.
 // body(b, item within the box) runs with every thread of the workgroup.
 // (Per-die queues, each die draining a contiguous range of items first so that
@@ -1329,18 +1329,17 @@ __device__ __forceinline__ void batch_loop(const uint32_t *__restrict__ first, i
 {
     __shared__ uint32_t s_item;
     const int tid = threadIdx.y * TW + threadIdx.x;
-    const uint32_t item0 = first[0], total = first[nbox] - item0;
+    const uint32_t total = first[nbox];
     if (blockIdx.x == 0 && tid == 0) counter[parity ^ 1] = 0u;
     for (uint32_t item = blockIdx.x; item < total;) {
-        const uint32_t k = item0 + item;
         int lo = 0, hi = nbox - 1;  // last box with first[b] <= item
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (first[mid] <= k) lo = mid;
+            if (first[mid] <= item) lo = mid;
             else hi = mid - 1;
         }
         const int b = __builtin_amdgcn_readfirstlane(lo);
-        body(b, k - first[b]);
+        body(b, item - first[b]);
         if (total <= gridDim.x) break;
         if (tid == 0) s_item = gridDim.x + atomicAdd(&counter[parity], 1u);
         __syncthreads();  // the item's LDS traffic is over
