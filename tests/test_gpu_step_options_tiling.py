@@ -53,3 +53,14 @@ def test_same_bits_for_every_decomposition(shape, opt):
     # the options act: the fields are not those of the plain step
     plain = fields_after(shape, None, 4, storage=opt.get("storage", "f32"))
     assert not np.array_equal(plain["u"], ref["u"]) and np.isfinite(ref["u"]).all()
+
+
+@pytest.mark.parametrize("storage", ["f16", "f32"])
+@pytest.mark.parametrize("shape", [(31, 51, 84), (44, 49, 82), (90, 30, 66), (30, 30, 96)])
+def test_same_bits_for_small_ragged_boxes(shape, storage):
+    # by default one round of 32-wide items for some of these, 64-wide ones for others
+    ref = fields_after(shape, (64, 2), 2, storage=storage)
+    for tiling in (None, (32, 1)):
+        m = fields_after(shape, tiling, 2, storage=storage)
+        for k in ref:
+            assert np.array_equal(ref[k], m[k]), (k, tiling)
