@@ -603,9 +603,9 @@ int default_tile(const lbm_batch *b)
 // Planes per work item where none is asked for: the length that brings the
 // launch through its rounds of resident workgroups soonest, a round costing its
 // planes and, for the phase field's prologue, about three more.  A small box is
-// cut into enough items for every compute unit (64^3 two-phase FP32: 26 us at 2
-// planes, 134 at 32; 32^3 single phase: 9 and 38); a large one keeps the
-// longest item that still runs at full rate: longer ones leave the
+// cut into enough items for every compute unit (64^3 two-phase FP32: 21 us a step at 2
+// planes, 132 at 32; single phase: 13 and 43); a large one keeps the longest item
+// that still runs at full rate (single phase FP32 none but 2): longer ones leave the
 // last round idle and spread the planes in flight over more of memory (512^3
 // FP32: 6.75 ms at 16 planes, 6.92 at 32; with the learned curvature, whose pass
 // checks and stages every item, 7.25 at 16, 7.15 at 32; FP16: 4.61 at 32, 4.79

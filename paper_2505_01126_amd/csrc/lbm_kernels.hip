@@ -565,7 +565,8 @@ __device__ __forceinline__ void read_tile(const Params &P, const void *fin_, con
 
 template <int S, bool FRC, bool ML, bool FX, bool ROW, bool NT>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ML || !ROW ? 3 : 4)))
-k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, float *u, double *phi_out, int chunk, int wx)
+k_moments(Params P, const void *fin, const void *phi, float *rho, float *pr, float *u, double *phi_out, int chunk,
+          int wx)
 {
     __shared__ __align__(16) char mlp_raw[ML ? sizeof(MlpW) + (NTHREADS / 64) * sizeof(MlpWave) : 1];
     MlpW &W = *(MlpW *)mlp_raw;

@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const uint16_t *__restrict_
 // by sample, they took 128 reads of 2 bytes per lane).  gW3 = d3^T h2 keeps d3 in
 // FP32 on the FP32 MFMA; the bias gradients are one more column of ones in the
 // products.  The weights are read 16 bytes at a time.  16384 samples: 23.1 ->
-// 15.3 us.
+// 14.6 us.
 struct BLds {
     WLds W;
     _Float16 h[4][16][HP];  // each wave's activations, then its d2, by sample
@@ -260,7 +260,7 @@ __global__ void __launch_bounds__(256) k_mlp_backward(const uint16_t *__restrict
 // Sums of the block partials: 32 values per workgroup, 16 threads to a value,
 // each every 16th partial, then a tree in a fixed order.  Bound by the latency
 // of its loads (6.4 MB for 256 partials): one thread per value, adding them one
-// after the other, took 58.7 us, this 4.9 us.
+// after the other, took 58.7 us, this 4.3 us.
 constexpr int RED_VALS = 32, RED_THREADS = 16;
 __global__ void __launch_bounds__(RED_VALS *RED_THREADS)
     k_mlp_reduce(const float *__restrict__ partial, int nblocks, float inv_b, float *__restrict__ grad,
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(256) k_mlp_adam(float *__restrict__ w, float *
 // the list over the threads: one thread per column of a row (a row is one
 // 64-byte store, and the loads of 64 rows are in flight at once) and one thread
 // per label.  Bound by those chains of loads: 4096 rows of a 48^3 box of four
-// spheres took 12.9 us with one thread per row, 8.9 us here, and the call, with
+// spheres took 12.9 us with one thread per row, 7.4 us here, and the call, with
 // one wait and no upload, 79 -> 56 us.
 __device__ __forceinline__ bool is_interface(double p) { return p > 0.02 && p < 0.98; }
 

@@ -167,10 +167,12 @@ template <class T> __device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, 
 // reads them before the next launch, by which time a 512^3 state has long left
 // L2 and the Infinity Cache, so caching them only evicts input lines that
 // neighbouring work items still fetch (measured 2-4 % faster per step on
-// 512^3).  The step uses them only where the tile rows cover whole 128-byte
+// 512^3).  The step uses them for the boxes whose tile rows cover whole 128-byte
 // lines (a partial line written past the caches measured slower: a batch of
-// boxes with edges 32-96, 8 %) and the populations exceed the Infinity Cache,
-// which otherwise holds them for the next step.  Loads keep the default
+// boxes with edges 32-96, 8 %) where the batch's populations exceed the Infinity
+// Cache, which otherwise holds them for the next step.  (In a batch with both kinds
+// of box each kind is a launch of its own: a policy per box inside one launch
+// doubles the plane loop, which then spilled 20-80 registers.)  Loads keep the default
 // policy: non-temporal loads measured slower.
 constexpr int STORE_NT = 2;
 template <class T, int AUX = 0>
@@ -569,7 +571,7 @@ __device__ __forceinline__ void plane3(const float *v, P3 &p)
 
 // ----------------------------------------------------------------- forcing
 // Time-independent body acceleration (Sec. 5.1 uses a fixed large-scale
-// field).  The host groups the modes by |kx| and folds the y and z phases into
+// field).  k_forcing groups the modes by |kx| and folds the y and z phases into
 // per-row coefficients (see lbm_internal.h); a site combines its row's 15
 // coefficients with the x twiddles ex = (cos t, sin t, cos 2t, sin 2t).
 // UNIFORM: the row is the same in every lane of the wave (one x-row per wave);
@@ -600,9 +602,9 @@ __device__ __forceinline__ void forcing_at(const Params &P, float4 ex, uint32_t 
 constexpr int HX = 3, HY = 3;                  // phi tile halo (WENO-5 needs 3)
 constexpr int NRING = 7;                       // phi planes z-3 .. z+3
 
-// Workgroup tile of TW x (256 / TW) sites: TW = 64 is one wave per x-row (the
-// single-box kernel); TW = 32 puts two rows in a wave (boxes of 32 or 96 sites
-// in x waste no lanes).  LDS tiles and per-thread work rounds derive from it.
+// Workgroup tile of TW x (256 / TW) sites: TW = 64 is one wave per x-row;
+// TW = 32 puts two rows in a wave (boxes of 32 or 96 sites in x waste no lanes).
+// LDS tiles and per-thread work rounds derive from it.
 template <int TW> struct Tile {
     static constexpr int X = TW, Y = NTHREADS / TW;
     static constexpr int PX = X + 2 * HX, PY = Y + 2 * HY;
@@ -638,8 +640,8 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 // the phi plane z+4, the face velocities of plane z+1, the 27 populations of
 // plane z+1 and the site's own phi and u_z ahead are already being fetched.
 //
-// What bounds it: with 16-bit populations the vector instructions (937 per site
-// and plane, issued 88 % of the time with three waves per SIMD), with FP32 ones
+// What bounds it: with 16-bit populations the vector instructions (934 per site
+// and plane, issued 90 % of the time with three waves per SIMD), with FP32 ones
 // the memory traffic.  Hence: the phi stencil is summed plane by plane, each
 // plane once for the Q, the gradient and the Hessian of the three planes it
 // enters (summed anew for each, they were 110 instructions more); every address
@@ -647,7 +649,7 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 // exact, so that neither the stores of a plane nor the loads of the next are
 // waited for before they are needed.  512^3 bubbly HIT, per step: FP16 5.0 ->
 // 4.6 ms; 256^3 single phase FP16 0.575 -> 0.47 ms; Runge-Kutta stage at 256^3
-// 0.385 -> 0.35 ms; FP32 at 512^3 6.9 ms as before.
+// 0.385 -> 0.35 ms; FP32 at 512^3 as before.
 // One work item: the xy tile and z chunk with linear index L (x tile fastest,
 // then y tile, then z chunk) of one box.  Every thread of the workgroup calls
 // it; it leaves no LDS state that the next call relies on.
