@@ -155,9 +155,13 @@ bool thin(const Params &p, int tenths)
 // Fields too large to stay in the caches until they are read are stored
 // non-temporally.  The initial phi and u of a box from 1.18 M sites on: set-up and
 // first step of 400 x 400 x 60 1.14 ms, 1.19 cached; of 32^3 to 64^3 up to 10 us
-// less cached.  The fields of a read-out from 256 MB on, and those of rows, which are
-// whole lines: FP32 read-out of 250^3 and a pass over u and phi 0.56 ms, 0.62 cached; of
-// 129 x 130 x 131 82 and 79 us; of 512^3 alone, 4.00 ms, 4.13 cached.
+// less cached.  The fields of a read-out whose rows are whole lines (512^3: 4.00 ms, 4.13
+// cached), and those that do not fit the 256 MB Infinity Cache together with the
+// state they are read from: cached, they push out what the next step or read-out
+// needs (268 x 40 x 207 FP32, set-up and read-out: 227 us, 237 cached; 190 x 130 x 170
+// FP16, read-outs alone: 85 us, 94 cached; a pass over u and phi after each costs 2-5 %
+// more then, up to 250^3, where it gains 10).  Below, cached fields are as fast to
+// write and 2-4 % faster to use (129 x 120 x 116 FP32: 72 us with the pass, 75).
 bool large(const Params &p, int64_t sites) { return (int64_t)p.nx * p.ny * p.nz >= sites; }
 // Set-up.  By sites on thin planes (8 x 8 x 65536: 321 us against 570; 17 x 17 x
 // 4000: 127 and 140); 20 x 20, which fills 0.78 of the lanes, is even, and full
@@ -184,7 +188,7 @@ Plan plan_read(const Params &p, int storage, bool fields)
 {
     if (!p.two_phase) return {true, 0, 0};
     const int wx = march_wx(p, storage != 0);
-    const bool nt = wx || large(p, 256000000 / 28);
+    const bool nt = wx || large(p, 256000000 / (27 * (storage ? 2 : 4) + 36));
     if (p.curv_mode == 1) {
         const int c = march_chunk(p, wx, 6);
         return {thin(p, 8) || (fields && c < 2), wx, c, nt};
