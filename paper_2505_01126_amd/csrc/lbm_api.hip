@@ -553,7 +553,11 @@ BatchOffsets batch_offsets(int n)
 // of the sites, all go that way (320^3 and 100^3: 1.77 ms, 1.89 all cached); where they
 // hold a quarter or more, they get a launch of their own (two of 256^3 and four of
 // 150^3: 2.93 ms, 3.18 all cached, 3.23 all non-temporal); below that all are cached
-// (128^3 and four of 200^3: 2.66 ms, 2.70 in two launches).
+// (128^3 and four of 200^3: 2.66 ms, 2.70 in two launches).  A second launch has a last
+// round of its own, which is too dear below thirteen times the cache (17 boxes of
+// 40^3 to 64^3 in BF16 with the network: 238 us a step, 216 in one launch; FP16 100^3
+// and 128^3: 4 of each 553 us against 531, 12 of each 1507 against 1575).
+constexpr double MALL = 256e6;
 void choose_groups(lbm_batch *b, int tile)
 {
     const int n = (int)b->m.size();
@@ -566,7 +570,8 @@ void choose_groups(lbm_batch *b, int tile)
         lines += v;
         nl++;
     }
-    if ((size_t)tile * elem_bytes(b->storage) % 128 != 0 || bytes <= 256e6) lines = 0.0;
+    if ((size_t)tile * elem_bytes(b->storage) % 128 != 0 || bytes <= MALL) lines = 0.0;
+    if (lines < 0.9 * bytes && bytes < 13.0 * MALL) lines = 0.0;
     b->groups = lines >= 0.25 * bytes && lines < 0.9 * bytes ? 2 : 1;
     b->group[0] = Group{0, b->groups == 2 ? nl : n, lines >= 0.25 * bytes};
     b->group[1] = Group{nl, n - nl, false};
